@@ -303,9 +303,9 @@ int spfel_weighted_residual(spfel_plan plan, const void *slices,
  * Both are spfel_merge_adjoint of the weights (values 1, weights d) on a
  * plan with n_model = 2N - 1 and the same points; A* D b is
  * spfel_merge_adjoint of b with weights d on the size-N plan.  One
- * application is three DFT contractions to L = 2N cells per axis (the
+ * application is three line transforms to L = 2N cells per axis (the
  * circular convolution then equals the linear one), a pointwise product with
- * the transformed kernel and three contractions back; conjugate gradients
+ * the transformed kernel and three line transforms back; conjugate gradients
  * solve up to 16 systems (one per lambda) at once, sharing every launch.
  *
  * An spfel_normal object holds the DFT tables, the transformed kernel and
@@ -317,8 +317,10 @@ int spfel_weighted_residual(spfel_plan plan, const void *slices,
  * stay on the device (no host synchronisation). */
 
 /* n_model odd in 3..511, domain SPFEL_REAL or SPFEL_COMPLEX, max_systems
- * 1..16, on HIP device `device`.  SPFEL_ENOMEM if the buffers (about
- * 8 (2N)^3 (max_systems + 1) bytes) do not fit. */
+ * 1..16, on HIP device `device`.  SPFEL_ENOMEM if the buffers
+ * (the transformed kernel and an intermediate as large, 4 (2N)^3 bytes each
+ * for REAL and twice that for COMPLEX, and four vectors per system) do not
+ * fit. */
 int spfel_normal_create(spfel_normal *out, int n_model, int domain,
                         int max_systems, int device);
 

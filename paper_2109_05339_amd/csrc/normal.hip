@@ -5,8 +5,11 @@
 // weights D on (2N - 1)^3 modes (REAL domain: A^T D A x = C * even(x), C the
 // cosine transform of D).  On a grid of L = 2N cells per axis the circular
 // convolution equals the linear one for |k - k'| <= N - 1 < L / 2, so one
-// application is three separable DFT contractions N -> L, a pointwise
-// product with the transformed kernel, and three contractions L -> N.
+// application is three separable line transforms N -> L, a pointwise
+// product with the transformed kernel, and three line transforms L -> N.
+// REAL domain: the transform of a real vector is Hermitian, so axis 2 keeps
+// its nonnegative half, and the even part of the vector is the real part of
+// its transform, taken before the product.
 // Conjugate gradients solve up to kMaxSystems systems (one per lambda) at
 // once, sharing every transform launch; the step sizes stay on the device.
 #include <cmath>
@@ -16,12 +19,14 @@
 #include <string>
 #include <vector>
 
+#include "dft.h"
 #include "internal.h"
 
 namespace spfel {
 
 constexpr int kMaxSystems = 16;
 constexpr int kDotBlocks = 256;
+constexpr int64_t kGroupBytes = (int64_t)208 << 20;
 
 struct Lambdas {
   float v[kMaxSystems];
@@ -29,12 +34,16 @@ struct Lambdas {
 
 struct Normal {
   int device = 0, N = 0, L = 0, domain = SPFEL_REAL, max_sys = 0;
-  float2 *F = nullptr;     // [N][L]  exp(-2 pi i k l / L)
-  float2 *G = nullptr;     // [L][N]  exp(+2 pi i k l / L) / L
-  float2 *Hm = nullptr;    // [2N-1][L] exp(-2 pi i m l / L)
-  float2 *That = nullptr;  // L^3: transform of the Toeplitz kernel
-  float2 *X1 = nullptr, *X2 = nullptr, *X3 = nullptr;   // transform intermediates
-  void *ve = nullptr;      // symmetrised input (REAL)
+  int group = 1;           // systems per transform launch
+  int Lh = 0;              // cells kept along axis 2: N + 1 (REAL) or L
+  DftTable F;              // modes -> grid, exp(-2 pi i k l / L)
+  DftTable G;              // grid -> modes, exp(+2 pi i k l / L) / L
+  DftTable Hm;             // the 2N - 1 modes of the kernel -> grid, as F
+  float2 *That = nullptr;  // [L][L][Lh]: transform of the Toeplitz kernel
+  // transform intermediates of a group, [group][N][N][Lh] and
+  // [group][N][L][Lh] (X3, [group][L][L][Lh],
+  // only where the fused axis-0 pass does not fit the LDS)
+  float2 *X1 = nullptr, *X2 = nullptr, *X3 = nullptr;
   void *x = nullptr, *r = nullptr, *p = nullptr, *Ap = nullptr;
   float *scal = nullptr;   // per system: rr, pAp, rr_new, spare
   float *part = nullptr;   // dot partial sums
@@ -51,7 +60,7 @@ static bool nlive(Normal *p) {
 }
 
 static void free_normal(Normal *p) {
-  void *bufs[] = {p->F, p->G, p->Hm, p->That, p->X1, p->X2, p->X3, p->ve,
+  void *bufs[] = {p->F.t, p->G.t, p->Hm.t, p->That, p->X1, p->X2, p->X3,
                   p->x, p->r, p->p, p->Ap, p->scal, p->part};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
@@ -59,35 +68,19 @@ static void free_normal(Normal *p) {
 
 // ---------------------------------------------------------------- kernels --
 
-// ve[s][k] = (v[s][k] + v[s][-k]) / 2 (REAL domain).
-__global__ __launch_bounds__(256) void symmetrise_kernel(const float *__restrict__ v, int N,
-                                                         int n, float *__restrict__ ve) {
-  const int64_t N3 = (int64_t)N * N * N;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * N3) return;
-  const int64_t s = t / N3, k = t - s * N3;
-  const int64_t a = k / ((int64_t)N * N), b = (k / N) % N, c = k % N;
-  const int64_t kr = ((N - 1 - a) * N + (N - 1 - b)) * N + (N - 1 - c);
-  ve[t] = 0.5f * (v[s * N3 + k] + v[s * N3 + kr]);
-}
-
-// X[s][j] *= That[j] (complex), j < L^3.
+// X[s][j] *= That[j] (complex), j < L3; drop_im: the imaginary part of X is
+// dropped first.
 __global__ __launch_bounds__(256) void kernel_product(float2 *__restrict__ X,
                                                       const float2 *__restrict__ T, int64_t L3,
-                                                      int n) {
+                                                      int n, int drop_im) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n * L3) return;
-  const float2 a = X[t], b = T[t % L3];
-  X[t] = make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// y[s] += lambda_s v[s] (float32 values; complex vectors count twice).
-__global__ __launch_bounds__(256) void add_lambda_kernel(float *__restrict__ y,
-                                                         const float *__restrict__ v, int64_t len,
-                                                         int n, Lambdas lam) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * len) return;
-  y[t] = fmaf(lam.v[t / len], v[t], y[t]);
+  float2 a = X[t];
+  const float2 b = T[t % L3];
+  if (drop_im)
+    X[t] = make_float2(a.x * b.x, a.x * b.y);
+  else
+    X[t] = make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
 // Partial sums of sum_k u[s][k] v[k'] (real parts of conj(u) v for complex
@@ -234,30 +227,45 @@ static dim3 grid_of(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 // y[s] = A* D A v[s] (+ lambda_s v[s]) for s < n.
 static hipError_t normal_apply(const Normal &nm, const void *v, int n, const Lambdas *lam,
                                void *y, hipStream_t st) {
-  const int N = nm.N, L = nm.L;
-  const int64_t N3 = (int64_t)N * N * N, L3 = (int64_t)L * L * L;
-  const bool cplx = nm.domain == SPFEL_COMPLEX;
-  const void *in = v;
-  if (!cplx) {
-    hipLaunchKernelGGL(symmetrise_kernel, grid_of(n * N3), dim3(256), 0, st,
-                       static_cast<const float *>(v), N, n, static_cast<float *>(nm.ve));
-    in = nm.ve;
+  if (n > nm.group) {   // in groups whose intermediates stay in the memory-side cache
+    const size_t vec = (size_t)nm.N * nm.N * nm.N * (nm.domain == SPFEL_COMPLEX ? 8 : 4);
+    for (int s0 = 0; s0 < n; s0 += nm.group) {
+      const int m = n - s0 < nm.group ? n - s0 : nm.group;
+      Lambdas part{};
+      for (int s = 0; lam && s < m; ++s) part.v[s] = lam->v[s0 + s];
+      hipError_t e = normal_apply(nm, static_cast<const char *>(v) + s0 * vec, m, lam ? &part : nullptr,
+                                  static_cast<char *>(y) + s0 * vec, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
-  hipError_t e = launch_contract(in, cplx, nm.F, nm.X1, 0, n * N * N, N, L, 1, st);
-  if (e == hipSuccess) e = launch_contract(nm.X1, true, nm.F, nm.X2, 0, n * N, N, L, L, st);
-  if (e == hipSuccess) e = launch_contract(nm.X2, true, nm.F, nm.X3, 0, n, N, L, L * L, st);
+  const int64_t N = nm.N, L = nm.L, Lh = nm.Lh;
+  const bool cplx = nm.domain == SPFEL_COMPLEX;
+  const int64_t cols = L * Lh;
+  DftEpilogue none, last;
+  hipError_t e = launch_dft(nm.F, cplx ? kCC : kRH, {n * N * N, 1, (int)N, (int)Lh}, v, nm.X1, none, st);
+  if (e == hipSuccess)
+    e = launch_dft(nm.F, kCC, {n * N * Lh, (int)Lh, (int)N, (int)L}, nm.X1, nm.X2, none, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel_product, grid_of(n * L3), dim3(256), 0, st, nm.X3, nm.That, L3, n);
-  e = launch_contract(nm.X3, true, nm.G, nm.X2, 0, n * L * L, L, N, 1, st);
-  if (e == hipSuccess) e = launch_contract(nm.X2, true, nm.G, nm.X1, 0, n * L, L, N, N, st);
-  if (e == hipSuccess) e = launch_contract(nm.X1, true, nm.G, y, cplx ? 0 : 1, n, L, N, N * N, st);
+  if (!nm.X3) {
+    e = launch_dft_normal(nm.F, nm.G, cplx, nm.X2, nm.That, n, cols, st);
+  } else {
+    e = launch_dft(nm.F, kCC, {n * cols, (int)cols, (int)N, (int)L}, nm.X2, nm.X3, none, st);
+    hipLaunchKernelGGL(kernel_product, grid_of(n * L * cols), dim3(256), 0, st, nm.X3, nm.That,
+                       L * cols, n, cplx ? 0 : 1);
+    if (e == hipSuccess)
+      e = launch_dft(nm.G, kCC, {n * cols, (int)cols, (int)L, (int)N}, nm.X3, nm.X2, none, st);
+  }
+  if (e == hipSuccess)
+    e = launch_dft(nm.G, kCC, {n * N * Lh, (int)Lh, (int)L, (int)N}, nm.X2, nm.X1, none, st);
   if (e != hipSuccess) return e;
   if (lam) {
-    const int64_t len = N3 * (cplx ? 2 : 1);
-    hipLaunchKernelGGL(add_lambda_kernel, grid_of(n * len), dim3(256), 0, st,
-                       static_cast<float *>(y), static_cast<const float *>(v), len, n, *lam);
+    last.lam_v = v;
+    last.lambda = lam->v;
+    last.systems = n;
+    last.cols_per_system = N * N;
   }
-  return hipGetLastError();
+  return launch_dft(nm.G, cplx ? kCC : kHR, {n * N * N, 1, (int)Lh, (int)N}, nm.X1, y, last, st);
 }
 
 // out[s * stride] = u[s] . v[s or shared], over len floats.
@@ -304,17 +312,28 @@ int spfel_normal_create(spfel_normal *out, int n_model, int domain, int max_syst
   const int64_t N = n_model, L = p->L, M = 2 * N - 1, n = max_systems;
   const int64_t N3 = N * N * N, L3 = L * L * L;
   const size_t vec = (size_t)N3 * (domain == SPFEL_COMPLEX ? 8 : 4);
+  const int64_t Lh = domain == SPFEL_COMPLEX ? L : N + 1, cols = L * Lh;
+  p->Lh = (int)Lh;
+  // systems per launch: their intermediates together about the memory-side
+  // cache (256 MB; 8 systems at N = 129 in groups of 2 / 4 / 8: 3.78 / 3.54 /
+  // 3.64 ms for three CG steps)
+  const int64_t per_system = (N * N * Lh + N * L * Lh) * 8;
+  p->group = (int)std::max<int64_t>(1, std::min<int64_t>(n, kGroupBytes / per_system));
+  const int64_t gr = p->group;
+  const size_t tab_f = dft_table_sizes(p->F, kToGrid, (n_model - 1) / 2, n_model);
+  const size_t tab_g = dft_table_sizes(p->G, kToModes, (n_model - 1) / 2, n_model);
+  const size_t tab_h = dft_table_sizes(p->Hm, kToGrid, n_model - 1, n_model);
+  const bool fused = dft_normal_fits(p->F, p->G, domain == SPFEL_COMPLEX);
   struct Req {
     void **ptr;
     size_t bytes;
-  } reqs[] = {{reinterpret_cast<void **>(&p->F), (size_t)N * L * 8},
-              {reinterpret_cast<void **>(&p->G), (size_t)L * N * 8},
-              {reinterpret_cast<void **>(&p->Hm), (size_t)M * L * 8},
-              {reinterpret_cast<void **>(&p->That), (size_t)L3 * 8},
-              {reinterpret_cast<void **>(&p->X1), (size_t)n * std::max(N * N * L, M * M * L) * 8},
-              {reinterpret_cast<void **>(&p->X2), (size_t)n * std::max(N * L * L, M * L * L) * 8},
-              {reinterpret_cast<void **>(&p->X3), (size_t)n * L3 * 8},
-              {&p->ve, (size_t)n * N3 * 4},
+  } reqs[] = {{reinterpret_cast<void **>(&p->F.t), tab_f},
+              {reinterpret_cast<void **>(&p->G.t), tab_g},
+              {reinterpret_cast<void **>(&p->Hm.t), tab_h},
+              {reinterpret_cast<void **>(&p->That), (size_t)(L * cols) * 8},
+              {reinterpret_cast<void **>(&p->X1), (size_t)std::max(gr * N * N * Lh, M * M * Lh) * 8},
+              {reinterpret_cast<void **>(&p->X2), (size_t)std::max(gr * N * cols, M * cols) * 8},
+              {reinterpret_cast<void **>(&p->X3), fused ? 0 : (size_t)(gr * L * cols) * 8},
               {&p->x, n * vec},
               {&p->r, n * vec},
               {&p->p, n * vec},
@@ -322,6 +341,7 @@ int spfel_normal_create(spfel_normal *out, int n_model, int domain, int max_syst
               {reinterpret_cast<void **>(&p->scal), (size_t)kMaxSystems * 4 * 4},
               {reinterpret_cast<void **>(&p->part), (size_t)kMaxSystems * kDotBlocks * 4}};
   for (auto &r : reqs) {
+    if (r.bytes == 0) continue;
     e = hipMalloc(r.ptr, r.bytes);
     if (e != hipSuccess) {
       *r.ptr = nullptr;
@@ -333,25 +353,10 @@ int spfel_normal_create(spfel_normal *out, int n_model, int domain, int max_syst
     }
     p->bytes += r.bytes;
   }
-  // DFT tables in float64, rounded once; phases reduced modulo L exactly
-  std::vector<float2> F(N * L), G(L * N), H(M * L);
-  auto cis = [&](long k, long l, double sign, double scale) {
-    long q = (k * l) % L;
-    if (q < 0) q += L;
-    const double a = 2.0 * M_PI * (double)q / (double)L;
-    return make_float2((float)(std::cos(a) * scale), (float)(sign * std::sin(a) * scale));
-  };
-  const long h = (n_model - 1) / 2;
-  for (long ki = 0; ki < N; ++ki)
-    for (long l = 0; l < L; ++l) {
-      F[ki * L + l] = cis(ki - h, l, -1.0, 1.0);
-      G[l * N + ki] = cis(ki - h, l, +1.0, 1.0 / (double)L);
-    }
-  for (long mi = 0; mi < M; ++mi)
-    for (long l = 0; l < L; ++l) H[mi * L + l] = cis(mi - (N - 1), l, -1.0, 1.0);
-  e = hipMemcpy(p->F, F.data(), F.size() * 8, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(p->G, G.data(), G.size() * 8, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(p->Hm, H.data(), H.size() * 8, hipMemcpyHostToDevice);
+  const double scale = 1.0 / (double)L;
+  e = dft_table_fill(p->F, -1, false, [](int) { return 1.0; });
+  if (e == hipSuccess) e = dft_table_fill(p->G, +1, false, [&](int) { return scale; });
+  if (e == hipSuccess) e = dft_table_fill(p->Hm, -1, false, [](int) { return 1.0; });
   if (prev != device) (void)hipSetDevice(prev);
   if (e != hipSuccess) {
     free_normal(p);
@@ -387,11 +392,14 @@ int spfel_normal_set_psf(spfel_normal h, const void *psf, void *stream) {
   if ((reinterpret_cast<uintptr_t>(psf) & (cplx ? 7 : 3)) != 0)
     return fail(SPFEL_EINVAL, "normal_set_psf: psf misaligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int M = 2 * p->N - 1, L = p->L;
-  // That = DFT_L of the kernel placed at m mod L: three contractions M -> L
-  hipError_t e = launch_contract(psf, cplx, p->Hm, p->X1, 0, M * M, M, L, 1, st);
-  if (e == hipSuccess) e = launch_contract(p->X1, true, p->Hm, p->X2, 0, M, M, L, L, st);
-  if (e == hipSuccess) e = launch_contract(p->X2, true, p->Hm, p->That, 0, 1, M, L, L * L, st);
+  const int64_t M = 2 * p->N - 1, L = p->L, Lh = p->Lh;
+  // That = DFT_L of the kernel placed at m mod L: three line transforms M -> L
+  const DftEpilogue none;
+  hipError_t e = launch_dft(p->Hm, cplx ? kCC : kRH, {M * M, 1, (int)M, (int)Lh}, psf, p->X1, none, st);
+  if (e == hipSuccess)
+    e = launch_dft(p->Hm, kCC, {M * Lh, (int)Lh, (int)M, (int)L}, p->X1, p->X2, none, st);
+  if (e == hipSuccess)
+    e = launch_dft(p->Hm, kCC, {L * Lh, (int)(L * Lh), (int)M, (int)L}, p->X2, p->That, none, st);
   if (e != hipSuccess) return hip_fail(e, "normal_set_psf: launch");
   p->psf_set = true;
   return SPFEL_OK;
