@@ -378,8 +378,8 @@ int spfel_normal_lcurve(spfel_normal nm, const void *x, const void *rhs,
  * Shrinkwrap replaces the support by the cells where the periodic Gaussian
  * blur (standard deviation sigma cells, unit sum, separable circular
  * convolution) of |rho| reaches tau times its maximum.
- * The transforms are separable DFT contractions (float32).  An spfel_phase
- * object holds the tables and intermediates for one N (about 28 N^3 bytes,
+ * The transforms are separable line transforms (float32).  An spfel_phase
+ * object holds the tables and intermediates for one N (24 to 28 N^3 bytes,
  * allocated at create; later calls allocate nothing); calls on one object
  * share them, so work on different streams must not overlap. */
 

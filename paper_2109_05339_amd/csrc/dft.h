@@ -67,6 +67,11 @@ struct DftEpilogue {
   const uint8_t *support = nullptr;
   int hio = 0, positivity = 0;
   float beta = 0.f;
+  // error of a phasing iteration (kCyclic, kCC): *err = sum of the first
+  // err_n partial sums over the sum of the next err_n, by the first block
+  const float *err_part = nullptr;
+  int err_n = 0;
+  float *err = nullptr;
 };
 hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const void *in, void *out,
                       const DftEpilogue &ep, hipStream_t s);
@@ -81,5 +86,17 @@ bool dft_phase_fits(const DftTable &tab);
 // product (the transform of the even part of a real vector).
 hipError_t launch_dft_normal(const DftTable &to_grid, const DftTable &to_modes, bool cplx,
                              float2 *X, const float2 *That, int n, int64_t cols, hipStream_t s);
+
+// Axis-0 pass of phasing in place on X ([n][cols] complex columns, cols =
+// n * (n/2 + 1): the nonnegative half of axis 2): forward transform, the
+// amplitude projection of the full spectrum and inverse transform.  part
+// receives dft_phase_parts(n) partial sums of (|F| - amp)^2 over the measured
+// coefficients, then as many of amp^2.
+int64_t dft_phase_parts(int n);
+hipError_t launch_dft_phase(const DftTable &fwd, const DftTable &inv, float2 *X, const float *amp,
+                            const uint8_t *measured, float *part, hipStream_t s);
+// The projection alone, in place on F (the same half spectrum [n][cols]).
+hipError_t launch_phase_projection(int n, float2 *F, const float *amp, const uint8_t *measured,
+                                   float *part, hipStream_t s);
 
 }  // namespace spfel

@@ -26,7 +26,10 @@
 // Measured on an application of the normal equations (N = 129, L = 258, 8
 // REAL systems): 7.1 ms by full complex tables (42% of the FP32 matrix rate
 // on eleven times the products), 0.72 ms here: axis-0 pass 312 us, axis 1
-// 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.
+// 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.  One phasing
+// iteration at N = 129: 329 us by full tables and full spectra, 70 us here
+// (axis-0 pass with the projection 26 us, the others 11 to 13 us each, half
+// of it matrix instructions).
 //
 // Lane layout of the instruction: lane t supplies A[t % 16][t / 16] and
 // B[t / 16][t % 16] and receives D[4 (t / 16) + j][t % 16], j = 0..3.
@@ -379,7 +382,38 @@ struct Tail {
   const uint8_t *support;
   int hio, positivity;
   float beta;
+  const float *err_part;
+  int err_n;
+  float *err;
 };
+
+// *err = (sum of part[0 .. n)) / (sum of part[n .. 2n)), in a fixed order, by
+// one block.
+__device__ inline void reduce_error(const float *__restrict__ part, int n, float *err) {
+  __shared__ float sh[2][kMaxWaves];
+  float e = 0.f, a = 0.f;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    e += part[i];
+    a += part[n + i];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    e += __shfl_xor(e, off);
+    a += __shfl_xor(a, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = e;
+    sh[1][threadIdx.x >> 6] = a;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+      e += sh[0][w];
+      a += sh[1][w];
+    }
+    *err = a > 0.f ? e / a : 0.f;
+  }
+}
 
 // Blocks take neighbouring column tiles at about the same time (the tiles of
 // one XCD are contiguous): strided tiles share cache lines at their edges,
@@ -398,6 +432,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t st = LINES ? 1 : B;
   const uint32_t c0 = (uint32_t)xcd_contiguous_block() * kCol;
+  if constexpr (KIND == kCyclic && IO == kCC) {
+    if (tail.err && blockIdx.x == 0) reduce_error(tail.err_part, tail.err_n, tail.err);
+  }
   if constexpr (LINES) {   // lanes along a line
     for (int sl = lane; sl < g.slots; sl += 64)
       for (int col0 = wave; col0 < kCol; col0 += 4 * nw) {
@@ -648,6 +685,167 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_normal_kernel(Geo f, Geo b
   }
 }
 
+// Amplitude projection of one coefficient f = F[k] of the half spectrum of a
+// real density and, with it, of F[-k] = conj f.  The next density is the real
+// part of the inverse transform, that is the inverse transform of the
+// Hermitian part (G[k] + conj G[-k]) / 2 of the projected spectrum: with
+// G[+-k] = amp[+-k] f / |f| where measured (amp where f = 0) and f elsewhere.
+// k2_self: the mirror image lies in the half spectrum itself and counts its
+// own error.
+struct Amps {
+  float a, am;        // amp[k], amp[-k]
+  bool seen, seen_m;  // measured
+};
+__device__ inline float2 project(float2 f, const Amps &m, bool k2_self, float &e, float &a2) {
+  const float mag = sqrtf(fmaf(f.x, f.x, f.y * f.y));
+  const float2 u = mag > 0.f ? make_float2(f.x / mag, f.y / mag) : make_float2(1.f, 0.f);
+  float w = 0.f, keep = 2.f;
+  if (m.seen) {
+    const float d = mag - m.a;
+    e = fmaf(d, d, e);
+    a2 = fmaf(m.a, m.a, a2);
+    w += m.a;
+    keep -= 1.f;
+  }
+  if (m.seen_m) {
+    if (!k2_self) {
+      const float d = mag - m.am;
+      e = fmaf(d, d, e);
+      a2 = fmaf(m.am, m.am, a2);
+    }
+    w += m.am;
+    keep -= 1.f;
+  }
+  return make_float2(0.5f * fmaf(w, u.x, keep * f.x), 0.5f * fmaf(w, u.y, keep * f.y));
+}
+
+// The amplitudes at (k0, k1, k2) and at its mirror image, axes of n.
+__device__ inline Amps load_amps(const float *__restrict__ amp, const uint8_t *__restrict__ measured,
+                                 uint32_t n, uint32_t k0, uint32_t k1, uint32_t k2) {
+  const uint32_t m0 = k0 ? n - k0 : 0, m1 = k1 ? n - k1 : 0, m2 = k2 ? n - k2 : 0;
+  const uint32_t o = (k0 * n + k1) * n + k2, om = (m0 * n + m1) * n + m2;
+  return {amp[o], amp[om], !measured || measured[o] != 0, !measured || measured[om] != 0};
+}
+
+// Sums e and a2 over the block (a fixed order) into part[block] and
+// part[gridDim + block].
+__device__ inline void store_error(float e, float a2, float *__restrict__ part) {
+  __shared__ float sh[2][kMaxWaves];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    e += __shfl_xor(e, off);
+    a2 += __shfl_xor(a2, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = e;
+    sh[1][threadIdx.x >> 6] = a2;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+      e += sh[0][w];
+      a2 += sh[1][w];
+    }
+    part[blockIdx.x] = e;
+    part[gridDim.x + blockIdx.x] = a2;
+  }
+}
+
+// Phasing, axis 0: the columns of the half spectrum are transformed,
+// projected and transformed back within the block.
+__global__ __launch_bounds__(64 * kMaxWaves) void dft_phase_kernel(Geo f, Geo b, float2 *X,
+                                                                   const float *__restrict__ amp,
+                                                                   const uint8_t *__restrict__ measured,
+                                                                   uint32_t cols,
+                                                                   float *__restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float4 *V1 = reinterpret_cast<float4 *>(smem);
+  float4 *V2 = V1 + f.slots * kPitch;
+  const uint32_t c0 = (uint32_t)xcd_contiguous_block() * kCol;
+  const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t n = f.H, half = n / 2 + 1, st = cols;
+  const uint32_t c = c0 + (lane & 15);
+  const bool ok = c < cols;
+  const uint32_t k1 = ok ? c / half : 0, k2 = ok ? c - k1 * half : 0;
+  const bool k2_self = k2 == 0 || 2 * k2 == n;
+  {
+    const int icol = tid & (kCol - 1), step = blockDim.x / kCol;
+    const bool iok = c0 + icol < cols;
+    const uint32_t base = iok ? c0 + icol : 0;
+    for (int s0 = tid / kCol; s0 < f.slots; s0 += 4 * step) {
+      Raw<kCyclic> raw[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) raw[u] = load_slot<kCyclic, kCC>(f, X, base, st, s0 + u * step, iok);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (s0 + u * step < f.slots) fold_slot<kCyclic, kCC>(f, raw[u], s0 + u * step, icol, V1);
+    }
+    for (int e = tid; e < b.slots * kCol; e += blockDim.x)
+      if (2 * (e / kCol) > (int)n) V2[(e / kCol) * kPitch + (e & 15)] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  float e = 0.f, a2 = 0.f;
+  Amps am[4][2];   // rows q and n - q of the lane
+  auto load_rows = [&](int rt) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t q = max(row_of<kCyclic>(f, rt, 4 * (lane >> 4) + j), 0);   // clamped: not used
+      am[j][0] = load_amps(amp, measured, n, q, k1, k2);
+      am[j][1] = load_amps(amp, measured, n, q ? n - q : 0, k1, k2);
+    }
+  };
+  if (wave < f.tiles) load_rows(wave);
+  __syncthreads();
+  auto fold2 = [&](int q, int col, const Sums<true> &a, const Amps &mp, const Amps &mm) {
+    if (!ok) {   // columns past the end: any finite values
+      V2[q * kPitch + col] = make_float4(0.f, 0.f, 0.f, 0.f);
+      return;
+    }
+    const float2 g = project(a.plus(), mp, k2_self, e, a2);
+    float2 h = make_float2(0.f, 0.f);
+    if (q > 0 && 2 * q < (int)n) h = project(a.minus(), mm, k2_self, e, a2);
+    V2[q * kPitch + col] = fold<kCC>(g, h);
+  };
+  for (int rt = wave; rt < f.tiles; rt += nw) {
+    if (rt != wave) load_rows(rt);
+    tile_rows<kCyclic, true, false>(f, rt, V1, [&](int q, int col, int j, const Sums<true> &a, const Sums<true> &) {
+      fold2(q, col, a, am[j][0], am[j][1]);
+    });
+  }
+  if (wave == nw - 1) {
+    const Amps a0 = load_amps(amp, measured, n, 0, k1, k2);
+    zero_row<kCyclic, true>(f, V1, [&](int q, int col, int, const Sums<true> &a, const Sums<true> &) {
+      fold2(q, col, a, a0, a0);
+    });
+  }
+  __syncthreads();
+  auto store = [&](int q, int, int, const Sums<true> &a, const Sums<true> &) {
+    if (!ok) return;
+    X[c + (uint32_t)q * st] = a.plus();
+    if (q > 0 && 2 * q < (int)n) X[c + (n - (uint32_t)q) * st] = a.minus();
+  };
+  for (int rt = wave; rt < b.tiles; rt += nw) tile_rows<kCyclic, true, false>(b, rt, V2, store);
+  if (wave == 0) zero_row<kCyclic, true>(b, V2, store);
+  store_error(e, a2, part);
+}
+
+// The projection alone (sizes whose fused pass does not fit the LDS).
+__global__ __launch_bounds__(256) void phase_projection_kernel(float2 *__restrict__ F,
+                                                               const float *__restrict__ amp,
+                                                               const uint8_t *__restrict__ measured,
+                                                               uint32_t n, uint32_t cols,
+                                                               float *__restrict__ part) {
+  const uint32_t half = n / 2 + 1;
+  const int64_t total = (int64_t)n * cols, stride = (int64_t)gridDim.x * 256;
+  float e = 0.f, a2 = 0.f;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+    const uint32_t k0 = (uint32_t)(i / cols), c = (uint32_t)(i - (int64_t)k0 * cols);
+    const uint32_t k1 = c / half, k2 = c - k1 * half;
+    F[i] = project(F[i], load_amps(amp, measured, n, k0, k1, k2), k2 == 0 || 2 * k2 == n, e, a2);
+  }
+  store_error(e, a2, part);
+}
+
 // --------------------------------------------------------------- host ----
 static int up(int v, int m) { return (v + m - 1) / m * m; }
 
@@ -763,6 +961,9 @@ hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const voi
   t.hio = ep.hio;
   t.positivity = ep.positivity;
   t.beta = ep.beta;
+  t.err_part = ep.err_part;
+  t.err_n = ep.err_n;
+  t.err = ep.err;
   switch (tab.kind * 4 + io) {
     case kToGrid * 4 + kCC: return dft_go<kToGrid, kCC>(tab, ln, in, out, t, s);
     case kToGrid * 4 + kRH: return dft_go<kToGrid, kRH>(tab, ln, in, out, t, s);
@@ -807,6 +1008,28 @@ hipError_t launch_dft_normal(const DftTable &f, const DftTable &b, bool cplx, fl
   else
     SPFEL_DFTN(false, false);
 #undef SPFEL_DFTN
+  return hipGetLastError();
+}
+
+static int64_t phase_cols(int n) { return (int64_t)n * (n / 2 + 1); }
+
+int64_t dft_phase_parts(int n) { return (phase_cols(n) + kCol - 1) / kCol; }
+
+bool dft_phase_fits(const DftTable &tab) { return 2 * fold_bytes(tab, true) <= kLdsMax - 256; }
+
+hipError_t launch_dft_phase(const DftTable &fwd, const DftTable &inv, float2 *X, const float *amp,
+                            const uint8_t *measured, float *part, hipStream_t s) {
+  const int n = fwd.H;
+  hipLaunchKernelGGL(dft_phase_kernel, dim3((unsigned)dft_phase_parts(n)), dim3(64 * waves_of(fwd.tiles)),
+                     2 * fold_bytes(fwd, true), s, geo_of(fwd), geo_of(inv), X, amp, measured,
+                     (uint32_t)phase_cols(n), part);
+  return hipGetLastError();
+}
+
+hipError_t launch_phase_projection(int n, float2 *F, const float *amp, const uint8_t *measured,
+                                   float *part, hipStream_t s) {
+  hipLaunchKernelGGL(phase_projection_kernel, dim3((unsigned)dft_phase_parts(n)), dim3(256), 0, s, F,
+                     amp, measured, (uint32_t)n, (uint32_t)phase_cols(n), part);
   return hipGetLastError();
 }
 

@@ -60,3 +60,42 @@ def test_normal_operator_against_float64_ffts(N, real, n):
         want = torch.fft.ifftn(torch.fft.fftn(e, s=(L, L, L)) * big)[:N, :N, :N]
         want = (want.real if real else want) + lams[s] * x
         assert rel(y[s], want) <= 2e-5, (s, rel(y[s], want))
+
+
+def phase_step(rho, amp, seen, sup, beta):
+    """One HIO step without positivity in float64, and its error."""
+    F = torch.fft.fftn(rho.double())
+    mag = F.abs()
+    a = amp.double()
+    d = seen.double()
+    err = ((mag - a).square() * d).sum() / (a.square() * d).sum()
+    G = torch.where(seen.bool(), a * F / mag, F)
+    v = torch.fft.ifftn(G).real
+    return torch.where(sup.bool(), v, rho.double() - beta * v), err
+
+
+# even and odd lengths: 2 and 3 the smallest; around one, two, four and eight
+# tiles of 16 rows; 602 (unfused axis-0 pass).  Amplitudes and mask have no
+# symmetry, so a coefficient and its mirror image are told apart.
+@pytest.mark.parametrize("N", [2, 3, 4, 7, 31, 32, 33, 34, 64, 65, 66, 100, 128, 129, 130, 258, 602])
+def test_phase_step_against_float64_ffts(N):
+    rho = randn(N, (N, N, N), True)
+    amp = randn(N + 1, (N, N, N), True).abs() * N ** 1.5
+    seen = (randn(N + 2, (N, N, N), True) > -0.7).to(torch.uint8)
+    sup = (randn(N + 3, (N, N, N), True) > 0).to(torch.uint8)
+    beta = 0.75
+    want, err = phase_step(rho, amp, seen, sup, beta)
+    got = rho.clone()
+    p = spfel.Phase(N, device=DEV)
+    e = p.iterate(got, amp, sup, 1, mode=spfel.PHASE_HIO, beta=beta, positivity=False, measured=seen,
+                  errors=True)
+    # a projected coefficient keeps its relative error unless |F| is small
+    # against its rounding; 2e-5 covers six passes as above
+    assert rel(got, want) <= 2e-5, rel(got, want)
+    assert abs(float(e[0]) - float(err)) <= 1e-5 * float(err)
+    # all coefficients measured
+    want, err = phase_step(rho, amp, torch.ones_like(seen), sup, beta)
+    got = rho.clone()
+    e = p.iterate(got, amp, sup, 1, mode=spfel.PHASE_HIO, beta=beta, positivity=False, errors=True)
+    assert rel(got, want) <= 2e-5, rel(got, want)
+    assert abs(float(e[0]) - float(err)) <= 1e-5 * float(err)
