@@ -222,7 +222,7 @@ static size_t alloc_bins(Plan *p, int64_t P) {
 
 static void free_plan(Plan *p) {
   free_bins(p);
-  void *bufs[] = {p->u, p->wpos, p->wneg, p->t1, p->t2, p->acc, p->partials, p->rot,
+  void *bufs[] = {p->u, p->to_grid.t, p->to_modes.t, p->t1, p->t2, p->acc, p->partials, p->rot,
                   p->det_sorted, p->det_perm};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
@@ -291,14 +291,15 @@ int spfel_plan_create(spfel_plan *out, int n_model, int kernel_width,
   const size_t N = n_model, nf = p->nf;
   const size_t el = domain == SPFEL_COMPLEX ? sizeof(float2) : sizeof(float);
   const size_t grid_b = nf * nf * nf * el;
-  const size_t tab_b = N * nf * sizeof(float2);
+  const size_t tab_grid = dft_table_sizes(p->to_grid, kToGrid, (n_model - 1) / 2, n_model);
+  const size_t tab_modes = dft_table_sizes(p->to_modes, kToModes, (n_model - 1) / 2, n_model);
   const size_t tmp_b = 4 * N * N * N * sizeof(float2);
   struct Req {
     void **ptr;
     size_t bytes;
   } reqs[] = {{&p->u, grid_b},
-              {reinterpret_cast<void **>(&p->wpos), tab_b},
-              {reinterpret_cast<void **>(&p->wneg), tab_b},
+              {reinterpret_cast<void **>(&p->to_grid.t), tab_grid},
+              {reinterpret_cast<void **>(&p->to_modes.t), tab_modes},
               {reinterpret_cast<void **>(&p->t1), tmp_b},
               {reinterpret_cast<void **>(&p->t2), tmp_b},
               {&p->acc, grid_b},
@@ -338,31 +339,11 @@ int spfel_plan_create(spfel_plan *out, int n_model, int kernel_width,
     delete p;
     return hip_fail(e, "plan_create: hipStreamCreate");
   }
-  // Transform tables in float64, rounded once to float32.  The phase index
-  // k l is reduced modulo nf exactly before the trigonometric evaluation.
   std::vector<double> ph(N);
   kernel_transform(n_model, p->nf, kernel_width, p->beta, ph.data());
-  const int h = (n_model - 1) / 2;
-  std::vector<float2> wp(N * nf), wn(nf * N);
-  // wpos writes the interpolation grid in centred storage (cell l at index
-  // (l + nf/2) mod nf): its phase is that of cell l = index - nf/2.
-  for (int ki = 0; ki < n_model; ++ki) {
-    const long k = ki - h;
-    for (int l = 0; l < p->nf; ++l) {
-      const long nl = (long)nf;
-      long r = (k * l) % nl, rc = (k * ((long)l - nl / 2)) % nl;
-      if (r < 0) r += nf;
-      if (rc < 0) rc += nf;
-      const double a = 2.0 * M_PI * (double)r / (double)nf;
-      const double ac = 2.0 * M_PI * (double)rc / (double)nf;
-      wp[(size_t)ki * nf + l] =
-          make_float2((float)(std::cos(ac) / ph[ki]), (float)(std::sin(ac) / ph[ki]));
-      wn[(size_t)l * N + ki] =
-          make_float2((float)(std::cos(a) / ph[ki]), (float)(-std::sin(a) / ph[ki]));
-    }
-  }
-  e = hipMemcpy(p->wpos, wp.data(), tab_b, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(p->wneg, wn.data(), tab_b, hipMemcpyHostToDevice);
+  const auto deconvolve = [&](int k) { return 1.0 / ph[(n_model - 1) / 2 + k]; };
+  e = dft_table_fill(p->to_grid, +1, true, deconvolve);
+  if (e == hipSuccess) e = dft_table_fill(p->to_modes, -1, false, deconvolve);
   if (e != hipSuccess) {
     free_plan(p);
     delete p;
@@ -523,10 +504,17 @@ int spfel_set_model(spfel_plan plan, const void *model, void *stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int N = p->N, nf = p->nf;
   // u[l] = sum_k m_k exp(+2 pi i k.l / nf) / (psi_hat psi_hat psi_hat), one
-  // axis at a time: axis 2 (N^2 lines), axis 1, axis 0.
-  hipError_t e = launch_contract(model, cplx, p->wpos, p->t1, 0, N * N, N, nf, 1, s);
-  if (e == hipSuccess) e = launch_contract(p->t1, true, p->wpos, p->t2, 0, N, N, nf, nf, s);
-  if (e == hipSuccess) e = launch_contract(p->t2, true, p->wpos, p->u, cplx ? 0 : 1, 1, N, nf, nf * nf, s);
+  // axis at a time: axis 2 (N^2 lines), axis 1, axis 0.  A real model's sum is
+  // Hermitian: its nonnegative half along axis 2 is enough until the last
+  // pass, which writes the real part at each cell and at its mirror image.
+  const int half = cplx ? nf : N + 1;
+  DftEpilogue none, last;
+  last.mirror1 = last.mirror2 = nf;
+  hipError_t e = launch_dft(p->to_grid, cplx ? kCC : kRH, {(int64_t)N * N, 1, N, half}, model, p->t1, none, s);
+  if (e == hipSuccess)
+    e = launch_dft(p->to_grid, kCC, {(int64_t)N * half, half, N, nf}, p->t1, p->t2, none, s);
+  if (e == hipSuccess)
+    e = launch_dft(p->to_grid, cplx ? kCC : kCRe, {(int64_t)nf * half, nf * half, N, nf}, p->t2, p->u, last, s);
   if (e != hipSuccess) return hip_fail(e, "set_model: launch");
   p->model_set = true;
   return SPFEL_OK;
@@ -835,20 +823,30 @@ int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
   const size_t nf = p->nf;
   const size_t grid_b = nf * nf * nf * (cplx ? sizeof(float2) : sizeof(float));
   hipError_t e = hipSuccess;
-  if (!p->pending) e = launch_fill_zero(p->acc, grid_b, s);
+  if (!p->pending && !p->acc_zero) e = launch_fill_zero(p->acc, grid_b, s);
+  p->acc_zero = false;
   if (e == hipSuccess && any) e = launch_spread(*p, quats, n_img, det_q, P, values, weights, s);
   if (e != hipSuccess) return hip_fail(e, "merge_adjoint: launch");
   p->pending = true;
   if (defer) return SPFEL_OK;
   p->pending = false;
   const int N = p->N, nfi = p->nf;
-  const bool acc = (flags & SPFEL_MERGE_ACCUMULATE) != 0;
   // f_k = sum_l v_l exp(-2 pi i k.l / nf) / (psi_hat psi_hat psi_hat),
-  // truncated to the N^3 modes: axis 2, axis 1, axis 0.
-  e = launch_contract(p->acc, cplx, p->wneg, p->t1, 0, nfi * nfi, nfi, N, 1, s);
-  if (e == hipSuccess) e = launch_contract(p->t1, true, p->wneg, p->t2, 0, nfi, nfi, N, N, s);
+  // truncated to the N^3 modes: axis 2 (which leaves acc zeroed for the next
+  // merge), axis 1, axis 0.  A real accumulator's modes are Hermitian: the
+  // nonnegative half along axis 2, then the real part at each mode and at its
+  // mirror image.
+  const int half = cplx ? N : (N + 1) / 2;
+  DftEpilogue first, none, last;
+  first.clear_in = true;
+  last.accumulate = (flags & SPFEL_MERGE_ACCUMULATE) != 0;
+  last.mirror1 = last.mirror2 = N;
+  e = launch_dft(p->to_modes, cplx ? kCC : kRH, {(int64_t)nfi * nfi, 1, nfi, half}, p->acc, p->t1, first, s);
+  p->acc_zero = e == hipSuccess;
   if (e == hipSuccess)
-    e = launch_contract(p->t2, true, p->wneg, out, cplx ? (acc ? 3 : 0) : (acc ? 2 : 1), 1, nfi, N, N * N, s);
+    e = launch_dft(p->to_modes, kCC, {(int64_t)nfi * half, half, nfi, N}, p->t1, p->t2, none, s);
+  if (e == hipSuccess)
+    e = launch_dft(p->to_modes, cplx ? kCC : kCRe, {(int64_t)N * half, N * half, nfi, N}, p->t2, out, last, s);
   return e == hipSuccess ? SPFEL_OK : hip_fail(e, "merge_adjoint: launch");
 }
 

@@ -3,10 +3,10 @@
 // equations and phasing.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 #include <functional>
-
-#include "internal.h"
 
 namespace spfel {
 
@@ -58,6 +58,7 @@ struct DftLines {
 // output, element for element.
 struct DftEpilogue {
   bool accumulate = false;
+  bool clear_in = false;   // zeros the lines once read (kToModes on contiguous lines)
   int mirror1 = 0, mirror2 = 0;
   const void *lam_v = nullptr;
   const float *lambda = nullptr;   // host values, one per system

@@ -29,7 +29,8 @@
 // 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.  One phasing
 // iteration at N = 129: 329 us by full tables and full spectra, 70 us here
 // (axis-0 pass with the projection 26 us, the others 11 to 13 us each, half
-// of it matrix instructions).
+// of it matrix instructions).  The merge's transform at N = 129: 515 us plus a
+// 17 us clear of the accumulator by full tables, 79 us here.
 //
 // Lane layout of the instruction: lane t supplies A[t % 16][t / 16] and
 // B[t / 16][t % 16] and receives D[4 (t / 16) + j][t % 16], j = 0..3.
@@ -37,8 +38,8 @@
 #include <cmath>
 #include <vector>
 
-#include "dft.h"
 #include "device_common.h"
+#include "internal.h"
 
 namespace spfel {
 
@@ -374,7 +375,7 @@ __device__ inline void zero_row(const Geo &g, const typename Vec<CPLX>::T *V, F 
 // ------------------------------------------------------------- kernel ----
 constexpr int kMaxLambdas = 16;
 struct Tail {
-  bool accumulate;
+  bool accumulate, clear_in;
   int mirror1, mirror2, half;
   const void *lam_v;
   float lambda[kMaxLambdas];
@@ -421,7 +422,7 @@ __device__ inline void reduce_error(const float *__restrict__ part, int n, float
 // wrote a third more bytes and took longer (183 against 146 us for a pass of
 // 138 MB -> 277 MB) for lack of wavefronts to hide its latencies.
 template <int KIND, int IO, bool LINES>
-__global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *__restrict__ in, void *out_,
+__global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *in, void *out_,
                                                              uint32_t cols, uint32_t B, int len_in,
                                                              int len_out, Tail tail) {
   constexpr bool C = IO == kCC;
@@ -464,6 +465,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
     }
   }
   __syncthreads();
+  if constexpr (KIND == kToModes && LINES && IO != kHR) {
+    if (tail.clear_in) {   // the block's lines are read: one range of the input
+      const uint32_t words = IO == kRH ? 1 : 2;
+      const uint32_t lo = c0 * (uint32_t)len_in * words;
+      const uint32_t hi = min(c0 + kCol, cols) * (uint32_t)len_in * words;
+      float *z = const_cast<float *>(static_cast<const float *>(in));
+      for (uint32_t o = lo + threadIdx.x; o < hi; o += blockDim.x) z[o] = 0.f;
+    }
+  }
   const uint32_t c_lane = c0 + (lane & 15);
   const uint32_t b_lane = LINES || c_lane >= cols ? 0 : col_base(c_lane, B, len_out);
   auto store = [&](int q, int col, int, const Sums<C> &a, const Sums<C> &b) {
@@ -951,6 +961,7 @@ hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const voi
   if (ln.cols <= 0) return hipSuccess;
   Tail t{};
   t.accumulate = ep.accumulate;
+  t.clear_in = ep.clear_in;
   t.mirror1 = ep.mirror1;
   t.mirror2 = ep.mirror2;
   t.half = ep.mirror1 > 0 ? (int)(ln.cols / ep.mirror1) : 1;

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <string>
 
+#include "dft.h"
 #include "spfel.h"
 
 namespace spfel {
@@ -23,12 +24,10 @@ struct Plan {
   // Fine grid the interpolation reads: nf^3 float (REAL) or float2
   // (COMPLEX), centred storage: cell l at index (l + nf/2) mod nf per axis.
   void *u = nullptr;
-  // Separable transform tables, float2, row-major [L][K] for a contraction
-  // over L producing K:
-  //   wpos [N][nf]: exp(+2 pi i k (l - nf/2) / nf) / psi_hat(k)  (model -> centred grid)
-  //   wneg [nf][N]: exp(-2 pi i k l / nf) / psi_hat(k)   (grid -> modes)
-  float2 *wpos = nullptr;
-  float2 *wneg = nullptr;
+  // Line transforms between the modes and the fine grid:
+  //   to_grid: exp(+2 pi i k (l - nf/2) / nf) / psi_hat(k)  (model -> centred grid)
+  //   to_modes: exp(-2 pi i k l / nf) / psi_hat(k)          (grid -> modes)
+  DftTable to_grid, to_modes;
   // Intermediates of the separable transforms, 4 N^3 float2 each.
   float2 *t1 = nullptr;
   float2 *t2 = nullptr;
@@ -63,6 +62,7 @@ struct Plan {
   size_t bin_bytes = 0;
   bool model_set = false;
   bool pending = false;  // deferred spreads are waiting in acc
+  bool acc_zero = false; // acc holds zeros (the transform that reads it clears it)
   size_t bytes = 0;
   // Events of the two-stream orientation pipeline (spfel_orient): the main
   // stream's start, each slice buffer's fill and release.

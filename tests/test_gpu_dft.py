@@ -16,7 +16,10 @@ import pytest
 import torch
 
 import paper_2109_05339_amd as spfel
-from tests._common import DEV
+import synth
+from oracle import geometry, nufft
+from tests._common import DEV, f32, gpu, host
+from tests._common import rel as rel_np
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +102,31 @@ def test_phase_step_against_float64_ffts(N):
     e = p.iterate(got, amp, sup, 1, mode=spfel.PHASE_HIO, beta=beta, positivity=False, errors=True)
     assert rel(got, want) <= 2e-5, rel(got, want)
     assert abs(float(e[0]) - float(err)) <= 1e-5 * float(err)
+
+
+# Model to fine grid (through slices) and fine grid to modes (through merges,
+# twice into one output: the transform leaves the accumulator zeroed), against
+# the oracle at the parity bar of the NUFFT tests; the model is not even.
+@pytest.mark.parametrize("N", [5, 7, 31, 33, 35, 63, 65, 67])
+@pytest.mark.parametrize("real", [True, False])
+def test_grid_transforms_against_oracle(real, N):
+    w = 4 if N < 9 else 6
+    m = synth.random_model(3, N, complex_model=not real)
+    m = m.astype(np.float32 if real else np.complex64)
+    q = synth.quaternions(synth.config(4), "image_quats", 3).astype(np.float32)
+    det = synth.detector_q(8).astype(np.float32)
+    x = geometry.slice_points(f32(q), f32(det)).reshape(-1, 3)
+    plan = spfel.Plan(N, kernel_width=w, domain=spfel.REAL if real else spfel.COMPLEX, device=DEV)
+    dt = torch.float32 if real else torch.complex64
+    plan.set_model(gpu(m, dt))
+    s = host(plan.slice(gpu(q), gpu(det))[0]).reshape(-1)
+    wide = m.astype(np.float64 if real else np.complex128)
+    assert rel_np(s, nufft.nufft2(wide, x, w=w, real=real)) <= 1e-5
+    g = np.random.default_rng(N)
+    y = g.standard_normal((3, 64)).astype(np.float32)
+    y = y if real else (y + 1j * g.standard_normal((3, 64))).astype(np.complex64)
+    want = nufft.nufft1(y.astype(np.float64 if real else np.complex128).ravel(), x, N, w=w, real=real)
+    out = plan.merge_adjoint(gpu(q), gpu(det), gpu(y, dt))
+    assert rel_np(host(out), want) <= 1e-5
+    plan.merge_adjoint(gpu(q), gpu(det), gpu(y, dt), out=out, flags=spfel.MERGE_ACCUMULATE)
+    assert rel_np(host(out), 2 * want) <= 1e-5
