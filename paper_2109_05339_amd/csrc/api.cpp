@@ -164,32 +164,33 @@ static bool aligned(const void *p, size_t a) {
 }
 
 static void free_bins(Plan *p) {
-  void *bufs[] = {p->bin_pts[0], p->bin_pts[1], p->bin_aux[0], p->bin_aux[1], p->bin_off[0],
-                  p->bin_off[1], p->bin_cur, p->bin_part, p->bin_sub[0], p->bin_sub[1],
-                  p->bin_nsub[0], p->bin_nsub[1]};
+  void *bufs[] = {p->bin_pts[0], p->bin_pts[1], p->bin_aux[0], p->bin_aux[1], p->bin_cnt,
+                  p->bin_cur, p->bin_sums, p->bin_sub[0], p->bin_sub[1], p->bin_nsub[0], p->bin_nsub[1]};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   for (int k = 0; k < 2; ++k) {
     p->bin_pts[k] = nullptr;
     p->bin_aux[k] = nullptr;
-    p->bin_off[k] = p->bin_nsub[k] = nullptr;
+    p->bin_nsub[k] = nullptr;
     p->bin_sub[k] = nullptr;
   }
-  p->bin_cur = p->bin_part = nullptr;
+  p->bin_cnt = p->bin_cur = nullptr;
+  p->bin_sums = nullptr;
   p->bin_cap = p->bin_batch = 0;
 }
 
 // Scratch of the binned spread for detectors of P points: batches of up to
-// 2^27 points (and at most 65,536 images), key counts and offsets,
+// 2^27 points (and at most 65,536 images), bin counts and cursors,
 // subproblem list, the spread's inputs twice (binning and spreading of
 // consecutive batches overlap).  Returns the bytes allocated, or 0 on
 // failure (nothing kept).
 static size_t alloc_bins(Plan *p, int64_t P) {
   const int64_t per = std::max<int64_t>(1, std::min<int64_t>(kBinBatchPoints / P, 65536));
   const int64_t cap = per * P;
-  const size_t keys = bin_keys(p->nf, p->w);
-  const size_t parts = (keys + 1023) / 1024;
-  const size_t subs = bin_max_subproblems(p->nf, p->w, cap);
+  const bool cplx = p->domain == SPFEL_COMPLEX;
+  const size_t bins = bin_count(p->nf, p->w);
+  // small batches are cut finer: at most 1,024 subproblems more
+  const size_t subs = bin_max_subproblems(p->nf, p->w, cplx, cap) + 1025;
   struct Req {
     void **ptr;
     size_t bytes;
@@ -197,10 +198,9 @@ static size_t alloc_bins(Plan *p, int64_t P) {
               {reinterpret_cast<void **>(&p->bin_pts[1]), (size_t)cap * sizeof(float4)},
               {reinterpret_cast<void **>(&p->bin_aux[0]), (size_t)cap * sizeof(uint2)},
               {reinterpret_cast<void **>(&p->bin_aux[1]), (size_t)cap * sizeof(uint2)},
-              {reinterpret_cast<void **>(&p->bin_off[0]), (keys + 1) * sizeof(int32_t)},
-              {reinterpret_cast<void **>(&p->bin_off[1]), (keys + 1) * sizeof(int32_t)},
-              {reinterpret_cast<void **>(&p->bin_cur), keys * sizeof(int32_t)},
-              {reinterpret_cast<void **>(&p->bin_part), parts * sizeof(int32_t)},
+              {reinterpret_cast<void **>(&p->bin_cnt), bins * sizeof(int32_t)},
+              {reinterpret_cast<void **>(&p->bin_cur), bins * sizeof(int32_t)},
+              {reinterpret_cast<void **>(&p->bin_sums), bin_scan_blocks(p->nf, p->w) * sizeof(int2)},
               {reinterpret_cast<void **>(&p->bin_sub[0]), subs * sizeof(int4)},
               {reinterpret_cast<void **>(&p->bin_sub[1]), subs * sizeof(int4)},
               {reinterpret_cast<void **>(&p->bin_nsub[0]), 256},
@@ -215,6 +215,7 @@ static size_t alloc_bins(Plan *p, int64_t P) {
     }
     total += r.bytes;
   }
+  p->bin_zero = false;
   p->bin_cap = cap;
   p->bin_batch = per;
   return total;

@@ -47,14 +47,14 @@ struct Plan {
   int64_t det_P = 0;
   // Binned spreading over the registered detector (allocated with it):
   // points of up to bin_batch images at a time, grouped by the fine-grid
-  // bin of their support origin and their axis-1 origin (the key).  Two
-  // sets of what the spread reads: batch b + 1 is binned into one while
-  // batch b spreads from the other.
+  // bin of their support origin.  Two sets of what the spread reads: batch
+  // b + 1 is binned into one while batch b spreads from the other.
   float4 *bin_pts[2] = {nullptr, nullptr};    // bin_cap: value (re), three kernel offsets
   uint2 *bin_aux[2] = {nullptr, nullptr};     // bin_cap: packed origin in the brick, value (im) bits
-  int32_t *bin_off[2] = {nullptr, nullptr};   // keys + 1: counts, then exclusive offsets
-  int32_t *bin_cur = nullptr;                 // keys: scatter cursors
-  int32_t *bin_part = nullptr;                // scan block totals
+  int32_t *bin_cnt = nullptr;                 // bins: points of the batch, cleared by the scan
+  mutable bool bin_zero = false;              // bin_cnt holds zeros (every queued count is followed by a scan)
+  int32_t *bin_cur = nullptr;                 // bins: scatter cursors
+  int2 *bin_sums = nullptr;                   // scan block totals (points, subproblems)
   int4 *bin_sub[2] = {nullptr, nullptr};      // subproblems (bin, first point, end)
   int32_t *bin_nsub[2] = {nullptr, nullptr};  // number of subproblems
   int64_t bin_cap = 0;           // points per batch
@@ -82,14 +82,16 @@ struct Plan {
 constexpr int kTile = 256;
 // Orientations per slicing launch (size of Plan::rot).
 constexpr int64_t kRotCap = 65536;
-// Binned spreading: brick side (cells), points per subproblem, points per
-// batch of images (2^27: 3.2 GB of staged points; every batch flushes each
-// occupied bin once, so larger batches flush less).
+// Binned spreading: brick side (cells), points per subproblem (three REAL or
+// two COMPLEX spreading blocks then fit a CU's LDS), points per batch of images (2^27: 3.2 GB of
+// staged points; every batch flushes each occupied bin once, so larger
+// batches flush less).
 constexpr int kBrick = 16;
-constexpr int kSubMax = 8192;
+constexpr int sub_cap(bool cplx) { return cplx ? 4096 : 3584; }
 constexpr int64_t kBinBatchPoints = (int64_t)1 << 27;
-size_t bin_keys(int nf, int w);
-size_t bin_max_subproblems(int nf, int w, int64_t cap);
+size_t bin_count(int nf, int w);
+size_t bin_scan_blocks(int nf, int w);
+size_t bin_max_subproblems(int nf, int w, bool cplx, int64_t points);
 
 // Status helpers: set the thread-local message and return the code.
 int fail(int code, const std::string &msg);
