@@ -45,8 +45,8 @@ struct Normal {
   // only where the fused axis-0 pass does not fit the LDS)
   float2 *X1 = nullptr, *X2 = nullptr, *X3 = nullptr;
   void *x = nullptr, *r = nullptr, *p = nullptr, *Ap = nullptr;
-  float *scal = nullptr;   // per system: rr, pAp, rr_new, spare
-  float *part = nullptr;   // dot partial sums
+  float *scal = nullptr;   // per system: r.r of even and of odd steps, alpha, spare (or lcurve's dots)
+  float *part = nullptr;   // two sets of dot partial sums
   bool psf_set = false;
   size_t bytes = 0;
 };
@@ -97,6 +97,7 @@ __global__ __launch_bounds__(256) void dot_partial_kernel(const float *__restric
   const int64_t lo = (int64_t)blockIdx.x * per, hi = min(len, lo + per);
   const float *us = u + s * len, *vs = v + s * v_stride;
   float acc = 0.f;
+#pragma unroll 4
   for (int64_t i = lo + threadIdx.x; i < hi; i += 256) acc = fmaf(us[i], vs[i], acc);
   sh[threadIdx.x] = acc;
   __syncthreads();
@@ -117,65 +118,118 @@ __global__ void dot_final_kernel(const float *__restrict__ part, int n, float *_
   out[s * stride] = t;
 }
 
-// CG start: x = x0, r = rhs + lambda x0 - Ap (Ap = A* D A x0 + lambda x0
-// already), p = r.
+// Vector passes of CG: block (b, s) takes the b-th contiguous range of system
+// s and leaves its part of a dot product (256 strided sums, a pairwise tree)
+// in part[s][b]; every block of the next pass adds the system's parts itself,
+// in one fixed order, so no pass of its own forms a step size.
+__device__ inline float block_sum(float v, float *sh) {
+  sh[threadIdx.x] = v;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
+    __syncthreads();
+  }
+  const float t = sh[0];
+  __syncthreads();
+  return t;
+}
+static_assert(kDotBlocks == 256, "one part per thread");
+
+// r = p = rhs - A* D A x0 (the lambda terms cancel, so every system starts
+// from the same residual), x = x0; part: r.r.
 __global__ __launch_bounds__(256) void cg_init_kernel(const float *__restrict__ rhs,
                                                       const float *__restrict__ x0,
-                                                      const float *__restrict__ Ap, int64_t len,
-                                                      int n, Lambdas lam, float *__restrict__ x,
-                                                      float *__restrict__ r,
-                                                      float *__restrict__ p) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * len) return;
-  const int64_t k = t % len;
-  const float v = fmaf(lam.v[t / len], x0[k], rhs[k]) - Ap[t];
-  x[t] = x0[k];
-  r[t] = v;
-  p[t] = v;
+                                                      const float *__restrict__ Ax0, int64_t len,
+                                                      float *__restrict__ x, float *__restrict__ r,
+                                                      float *__restrict__ p,
+                                                      float *__restrict__ part) {
+  __shared__ float sh[256];
+  const int s = blockIdx.y;
+  const int64_t per = (len + kDotBlocks - 1) / kDotBlocks;
+  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(len, lo + per);
+  x += s * len;
+  r += s * len;
+  p += s * len;
+  float acc = 0.f;
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
+    const float v = rhs[i] - Ax0[i];
+    x[i] = x0[i];
+    r[i] = v;
+    p[i] = v;
+    acc = fmaf(v, v, acc);
+  }
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) part[s * kDotBlocks + blockIdx.x] = acc;
 }
 
-// alpha = rr / pAp (0 once converged), x += alpha p, r -= alpha Ap.
-__global__ __launch_bounds__(256) void cg_update_kernel(const float *__restrict__ scal,
-                                                        const float *__restrict__ p,
-                                                        const float *__restrict__ Ap,
-                                                        int64_t len, int n,
-                                                        float *__restrict__ x,
-                                                        float *__restrict__ r) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * len) return;
-  const float *sc = scal + 4 * (t / len);
-  const float alpha = sc[1] > 0.f && sc[0] > 0.f ? sc[0] / sc[1] : 0.f;
-  x[t] = fmaf(alpha, p[t], x[t]);
-  r[t] = fmaf(-alpha, Ap[t], r[t]);
+// scal[s][0] = r.r of the start; hist[s][0] = |r|.
+__global__ __launch_bounds__(256) void cg_start_kernel(const float *__restrict__ part,
+                                                       float *__restrict__ scal,
+                                                       float *__restrict__ hist, int stride) {
+  __shared__ float sh[256];
+  const int s = blockIdx.x;
+  const float rr = block_sum(part[s * kDotBlocks + threadIdx.x], sh);
+  if (threadIdx.x == 0) {
+    scal[4 * s] = rr;
+    if (hist) hist[s * stride] = sqrtf(fmaxf(rr, 0.f));
+  }
 }
 
-// beta = rr_new / rr, p = r + beta p.
-__global__ __launch_bounds__(256) void cg_direction_kernel(const float *__restrict__ scal,
-                                                           const float *__restrict__ r,
-                                                           int64_t len, int n,
-                                                           float *__restrict__ p) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * len) return;
-  const float *sc = scal + 4 * (t / len);
-  const float beta = sc[0] > 0.f ? sc[2] / sc[0] : 0.f;
-  p[t] = fmaf(beta, p[t], r[t]);
+// alpha = rr / p.Ap (0 once converged), r -= alpha Ap; part_rr: r.r.  scal[s]:
+// rr of the even and of the odd steps, alpha.
+__global__ __launch_bounds__(256) void cg_residual_kernel(const float *__restrict__ part_pAp,
+                                                          float *__restrict__ scal, int it,
+                                                          const float *__restrict__ Ap, int64_t len,
+                                                          float *__restrict__ r,
+                                                          float *__restrict__ part_rr) {
+  __shared__ float sh[256];
+  const int s = blockIdx.y;
+  const float pAp = block_sum(part_pAp[s * kDotBlocks + threadIdx.x], sh);
+  const float rr = scal[4 * s + ((it - 1) & 1)];
+  const float alpha = pAp > 0.f && rr > 0.f ? rr / pAp : 0.f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) scal[4 * s + 2] = alpha;
+  const int64_t per = (len + kDotBlocks - 1) / kDotBlocks;
+  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(len, lo + per);
+  r += s * len;
+  Ap += s * len;
+  float acc = 0.f;
+#pragma unroll 4
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
+    const float v = fmaf(-alpha, Ap[i], r[i]);
+    r[i] = v;
+    acc = fmaf(v, v, acc);
+  }
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) part_rr[s * kDotBlocks + blockIdx.x] = acc;
 }
 
-// rr = rr_new; residual history hist[s][it] = sqrt(rr).
-__global__ void cg_advance_kernel(float *__restrict__ scal, int n, float *__restrict__ hist,
-                                  int it, int stride, int use_new) {
-  const int s = threadIdx.x;
-  if (s >= n) return;
-  if (use_new) scal[4 * s] = scal[4 * s + 2];
-  if (hist) hist[s * stride + it] = sqrtf(fmaxf(scal[4 * s], 0.f));
-}
-
-// x[s] = x0 for every system.
-__global__ __launch_bounds__(256) void broadcast_kernel(const float *__restrict__ x0, int64_t len,
-                                                        int n, float *__restrict__ x) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * len) return;
-  x[t] = x0[t % len];
+// beta = rr_new / rr; x += alpha p, p = r + beta p; hist[s][it] = |r|.
+__global__ __launch_bounds__(256) void cg_direction_kernel(const float *__restrict__ part_rr,
+                                                           float *__restrict__ scal, int it,
+                                                           const float *__restrict__ r, int64_t len,
+                                                           float *__restrict__ x,
+                                                           float *__restrict__ p,
+                                                           float *__restrict__ hist, int stride) {
+  __shared__ float sh[256];
+  const int s = blockIdx.y;
+  const float rr_new = block_sum(part_rr[s * kDotBlocks + threadIdx.x], sh);
+  const float rr = scal[4 * s + ((it - 1) & 1)], alpha = scal[4 * s + 2];
+  const float beta = rr > 0.f ? rr_new / rr : 0.f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    scal[4 * s + (it & 1)] = rr_new;
+    if (hist) hist[s * stride + it] = sqrtf(fmaxf(rr_new, 0.f));
+  }
+  const int64_t per = (len + kDotBlocks - 1) / kDotBlocks;
+  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(len, lo + per);
+  r += s * len;
+  x += s * len;
+  p += s * len;
+#pragma unroll 4
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
+    const float v = p[i];
+    x[i] = fmaf(alpha, v, x[i]);
+    p[i] = fmaf(beta, v, r[i]);
+  }
 }
 
 // d = x - x0 (x0 shared).
@@ -339,7 +393,7 @@ int spfel_normal_create(spfel_normal *out, int n_model, int domain, int max_syst
               {&p->p, n * vec},
               {&p->Ap, n * vec},
               {reinterpret_cast<void **>(&p->scal), (size_t)kMaxSystems * 4 * 4},
-              {reinterpret_cast<void **>(&p->part), (size_t)kMaxSystems * kDotBlocks * 4}};
+              {reinterpret_cast<void **>(&p->part), 2 * (size_t)kMaxSystems * kDotBlocks * 4}};
   for (auto &r : reqs) {
     if (r.bytes == 0) continue;
     e = hipMalloc(r.ptr, r.bytes);
@@ -460,28 +514,22 @@ int spfel_normal_solve(spfel_normal h, const void *rhs, const void *x0, int n,
   float *xf = static_cast<float *>(x_out), *r = static_cast<float *>(p->r);
   float *pp = static_cast<float *>(p->p), *Ap = static_cast<float *>(p->Ap);
   const int stride = iters + 1;
-  // x = x0 for every system, Ap = (A* D A + lambda) x0 on the batch of copies
-  hipLaunchKernelGGL(broadcast_kernel, grid_of(n * len), dim3(256), 0, st, x0f, len, n, xf);
-  hipError_t e = normal_apply(*p, xf, n, &lam, Ap, st);
+  const dim3 vec(kDotBlocks, (unsigned)n);
+  float *part_rr = p->part + kMaxSystems * kDotBlocks;
+  // A* D A x0 once: r = rhs + lambda x0 - (A* D A + lambda) x0 for every lambda
+  hipError_t e = normal_apply(*p, x0f, 1, nullptr, Ap, st);
   if (e != hipSuccess) return hip_fail(e, "normal_solve: launch");
-  hipLaunchKernelGGL(cg_init_kernel, grid_of(n * len), dim3(256), 0, st, rf, x0f, Ap, len, n, lam,
-                     xf, r, pp);
-  e = dots(*p, r, r, len, len, n, p->scal, 4, st);
-  if (e != hipSuccess) return hip_fail(e, "normal_solve: launch");
-  hipLaunchKernelGGL(cg_advance_kernel, dim3(1), dim3(64), 0, st, p->scal, n, residuals, 0,
-                     stride, 0);
+  hipLaunchKernelGGL(cg_init_kernel, vec, dim3(256), 0, st, rf, x0f, Ap, len, xf, r, pp, part_rr);
+  hipLaunchKernelGGL(cg_start_kernel, dim3((unsigned)n), dim3(256), 0, st, part_rr, p->scal, residuals,
+                     stride);
   for (int it = 1; it <= iters; ++it) {
     e = normal_apply(*p, pp, n, &lam, Ap, st);
-    if (e == hipSuccess) e = dots(*p, pp, Ap, len, len, n, p->scal + 1, 4, st);
     if (e != hipSuccess) return hip_fail(e, "normal_solve: launch");
-    hipLaunchKernelGGL(cg_update_kernel, grid_of(n * len), dim3(256), 0, st, p->scal, pp, Ap, len,
-                       n, xf, r);
-    e = dots(*p, r, r, len, len, n, p->scal + 2, 4, st);
-    if (e != hipSuccess) return hip_fail(e, "normal_solve: launch");
-    hipLaunchKernelGGL(cg_direction_kernel, grid_of(n * len), dim3(256), 0, st, p->scal, r, len,
-                       n, pp);
-    hipLaunchKernelGGL(cg_advance_kernel, dim3(1), dim3(64), 0, st, p->scal, n, residuals, it,
-                       stride, 1);
+    hipLaunchKernelGGL(dot_partial_kernel, vec, dim3(256), 0, st, pp, Ap, len, len, p->part);
+    hipLaunchKernelGGL(cg_residual_kernel, vec, dim3(256), 0, st, p->part, p->scal, it, Ap, len, r,
+                       part_rr);
+    hipLaunchKernelGGL(cg_direction_kernel, vec, dim3(256), 0, st, part_rr, p->scal, it, r, len, xf,
+                       pp, residuals, stride);
   }
   e = hipGetLastError();
   return e == hipSuccess ? SPFEL_OK : hip_fail(e, "normal_solve: launch");
