@@ -590,42 +590,53 @@ __global__ __launch_bounds__(512, 1) void match_bf16_big_kernel(
   };
 
   const int64_t steps = P / kBK2;
+  auto multiply = [&](int slot) {
+    // raised priority while issuing the MFMAs: the SIMD's other wavefront
+    // is then served between them, not ahead of them
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   issue(0, 0);
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's loads are in LDS
   __syncthreads();
+  if (steps > 1) issue(kBK2, 1);
+  frags(smem, smem + kBM2 * kBK2, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
   for (int64_t st = 0; st < steps; ++st) {
-    const int buf = (int)(st & 1);
-    if (st + 1 < steps) issue((st + 1) * kBK2, buf ^ 1);
-    const uint16_t *As = smem + buf * kStage2;
+    const uint16_t *As = smem + (st & 1) * kStage2;
     const uint16_t *Bs = As + kBM2 * kBK2;
-    frags(As, Bs, 0, 0);
 #pragma unroll
-    for (int kk = 0; kk < kBK2 / 16; ++kk) {
+    for (int kk = 0; kk < 3; ++kk) {
       // the scheduling barriers keep the next slice's reads ahead of this
       // slice's MFMAs (the compiler would otherwise sink them to save
       // registers and stall every MFMA group on a fresh LDS read)
-      if (kk + 1 < kBK2 / 16) {
-        frags(As, Bs, kk + 1, (kk + 1) & 1);
-        // LDS reads complete in order: this slice's 6 are in once at most
-        // the next slice's 6 are outstanding
-        __builtin_amdgcn_s_waitcnt(0xC67F);   // lgkmcnt(6), vmcnt/expcnt not waited
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // raised priority while issuing the MFMAs: the SIMD's other wavefront
-      // is then served between them, not ahead of them
-      __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][i], fb[kk & 1][j],
-                                                              acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
+      frags(As, Bs, kk + 1, (kk + 1) & 1);
+      // LDS reads complete in order: this slice's 6 are in once at most
+      // the next slice's 6 are outstanding
+      __builtin_amdgcn_s_waitcnt(0xC67F);   // lgkmcnt(6), vmcnt/expcnt not waited
+      multiply(kk & 1);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    // This stage's last fragments are in registers and the next stage is in
+    // LDS (vmcnt(0), lgkmcnt(0)) before the barrier; after it, the stage's
+    // buffer is free for the step after next, and the next step's first
+    // fragments are read ahead of this step's last MFMAs.
+    __builtin_amdgcn_s_waitcnt(0x0070);
     __syncthreads();
+    if (st + 2 < steps) issue((st + 2) * kBK2, (int)(st & 1));
+    if (st + 1 < steps) {
+      const uint16_t *An = smem + ((st + 1) & 1) * kStage2;
+      frags(An, An + kBM2 * kBK2, 0, 0);
+    }
+    multiply(1);
   }
+  __syncthreads();
 
   // Epilogue (LDS reused): norms of the tile's rows and columns, then each
   // column's 8 smallest proxies; candidate words carry the row in 8 bits.
