@@ -13,6 +13,8 @@
 //         float32 those whose lower bound can beat the running best, and
 //         certifies that no other model image can; images it cannot
 //         certify are matched again against every model image in float32.
+#include <algorithm>
+
 #include "device_common.h"
 #include "internal.h"
 
@@ -52,25 +54,28 @@ constexpr int kBK = 32;         // floats of P per K step
 constexpr int kLdF = kBK + 4;   // LDS row stride (floats)
 
 // Four consecutive values X[r][k..k+3] of a row of length ld, zero beyond
-// row `rows` or column `kend` (kend <= ld).  vec: 16-byte aligned rows and
-// kend % 4 == 0, so a quad is either wholly inside or wholly outside.
+// row `rows` or column `kend` (kend <= ld).  Whole quads take one load at
+// whatever alignment the row has (odd row lengths, such as a detector behind
+// a beam stop, leave rows on 4-byte boundaries; loading their values one by
+// one took 2.3 times as long on 512 x 256 x 4,095).
 __device__ inline float4 load_row4(const float *__restrict__ X, int64_t rows, int64_t r,
-                                   int64_t kend, int64_t k, bool vec, int64_t ld) {
-  if (r >= rows) return make_float4(0.f, 0.f, 0.f, 0.f);
+                                   int64_t kend, int64_t k, int64_t ld) {
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (r >= rows) return v;
   const float *p = X + r * ld + k;
-  if (vec) return k < kend ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 v;
+  if (k + 4 <= kend) {
+    __builtin_memcpy(&v, p, 16);
+    return v;
+  }
   v.x = k < kend ? p[0] : 0.f;
   v.y = k + 1 < kend ? p[1] : 0.f;
   v.z = k + 2 < kend ? p[2] : 0.f;
-  v.w = k + 3 < kend ? p[3] : 0.f;
   return v;
 }
 
 // Split-K: block (split, tile) covers K range [split kchunk, (split+1)
-// kchunk).  Every split stores its partial tile; the last split of a tile
-// to arrive (per-tile counter) adds the partials in split order (a fixed
-// order, so results do not depend on arrival order) and runs the epilogue.
+// kchunk) and stores its partial tile, row-major; reduce_f32_kernel adds the
+// partials in split order and runs the epilogue.
 //
 // 512 threads = 8 wavefronts as 2 (M) x 4 (N); each wavefront owns a 64 x 32
 // quarter-column of the 128 x 128 tile (two 32x32 MFMA accumulators plus two
@@ -81,14 +86,13 @@ constexpr int kF32Threads = 512;
 __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) void match_f32_kernel(
     const float *__restrict__ S, const float *__restrict__ D, const float *__restrict__ sn,
     const float *__restrict__ dn, int64_t M, int64_t N, int64_t P, uint32_t m_offset,
-    unsigned long long *__restrict__ keys, int tiles_m, int tiles_n, int vec, int splits,
-    int64_t kchunk, float *__restrict__ partials, unsigned *__restrict__ counters) {
+    unsigned long long *__restrict__ keys, int tiles_m, int tiles_n, int splits, int64_t kchunk,
+    float *__restrict__ partials) {
   // double-buffered A/B stages: one barrier per K step
   __shared__ __attribute__((aligned(16))) float As[2][kBM * kLdF];
   __shared__ __attribute__((aligned(16))) float Bs[2][kBN * kLdF];
   __shared__ float sns[kBM], dns[kBN];
   __shared__ unsigned long long red[2][kBN];
-  __shared__ unsigned arrived;
 
   int tm, tn, split;
   tile_of_block(tiles_m, tiles_n, splits, tm, tn, split);
@@ -103,8 +107,8 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int id = tid + kF32Threads * i, r = id >> 3, c = (id & 7) * 4;
-      ra[i] = load_row4(S, M, row0 + r, kend, k0 + c, vec, P);
-      rb[i] = load_row4(D, N, col0 + r, kend, k0 + c, vec, P);
+      ra[i] = load_row4(S, M, row0 + r, kend, k0 + c, P);
+      rb[i] = load_row4(D, N, col0 + r, kend, k0 + c, P);
     }
   };
 
@@ -164,36 +168,13 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 
   if (splits > 1) {
-    // publish this split's partial tile, then let the last arrival finish
-    const int tile = tm * tiles_n + tn;
-    float *mine = partials + ((int64_t)tile * splits + split) * (kBM * kBN);
+    float *mine = partials + ((int64_t)(tm * tiles_n + tn) * splits + split) * (kBM * kBN);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mine[(i * 16 + r) * kF32Threads + tid] = acc[i][r];
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) arrived = atomicAdd(counters + tile, 1u);
-    __syncthreads();
-    if (arrived != (unsigned)(splits - 1)) return;
-    __threadfence();
-    floatx16 sum[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum[i][r] = 0.f;
-    for (int sp = 0; sp < splits; ++sp) {
-      const float *part = partials + ((int64_t)tile * splits + sp) * (kBM * kBN);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          sum[i][r] += sp == split ? acc[i][r]
-                                   : __builtin_nontemporal_load(&part[(i * 16 + r) * kF32Threads + tid]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) acc[i] = sum[i];
-    if (tid == 0) counters[tile] = 0u;  // ready for the next launch
+      for (int r = 0; r < 16; ++r)
+        mine[(wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * kBN + wn * 32 + lr] = acc[i][r];
+    return;
   }
   if (tid < kBM) {
     sns[tid] = row0 + tid < M ? sn[row0 + tid] : 0.f;
@@ -231,6 +212,53 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 }
 
+// Sum of element (row, col) of a tile's partials in split order.
+__device__ inline float split_sum(const float *__restrict__ part, int splits, int row, int col) {
+  const float *p = part + row * kBN + col;
+  float v = 0.f;
+#pragma unroll 4
+  for (int sp = 0; sp < splits; ++sp) v += p[(int64_t)sp * (kBM * kBN)];
+  return v;
+}
+
+// Epilogue of a split launch: a block takes 32 columns of a tile, a thread 16
+// rows of one of them.
+constexpr int kRedCols = 32, kRedRows = kBM / (256 / kRedCols);
+
+__global__ __launch_bounds__(256) void reduce_f32_kernel(
+    const float *__restrict__ partials, int splits, const float *__restrict__ sn,
+    const float *__restrict__ dn, int64_t M, int64_t N, uint32_t m_offset, int tiles_n,
+    unsigned long long *__restrict__ keys) {
+  __shared__ unsigned long long red[256];
+  const int tile = blockIdx.x / (kBN / kRedCols), c0 = (blockIdx.x % (kBN / kRedCols)) * kRedCols;
+  const int col = c0 + (threadIdx.x & (kRedCols - 1)), rg = threadIdx.x / kRedCols;
+  const int64_t row0 = (int64_t)(tile / tiles_n) * kBM, n = (int64_t)(tile % tiles_n) * kBN + col;
+  const float *part = partials + (int64_t)tile * splits * (kBM * kBN);
+  unsigned long long best = ~0ull;
+  if (n < N) {
+    const float dnn = dn[n];
+#pragma unroll 4
+    for (int j = 0; j < kRedRows; ++j) {
+      const int row = rg * kRedRows + j;
+      if (row0 + row >= M) break;
+      const float d = fmaf(-2.0f, split_sum(part, splits, row, col), sn[row0 + row] + dnn);
+      const unsigned long long key =
+          ((unsigned long long)float_key(d) << 32) | (uint32_t)(m_offset + (uint32_t)(row0 + row));
+      best = key < best ? key : best;
+    }
+  }
+  red[threadIdx.x] = best;
+  __syncthreads();
+  if (threadIdx.x < kRedCols && n < N) {
+#pragma unroll
+    for (int k = 1; k < 256 / kRedCols; ++k) {
+      const unsigned long long o = red[threadIdx.x + k * kRedCols];
+      best = o < best ? o : best;
+    }
+    if (best != ~0ull) atomicMin(keys + n, best);
+  }
+}
+
 __global__ void pack_keys_kernel(const int32_t *__restrict__ idx, const float *__restrict__ dist,
                                  unsigned long long *__restrict__ keys, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -263,43 +291,30 @@ hipError_t launch_unpack_keys(const unsigned long long *keys, int32_t *idx, floa
 
 static bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Resident blocks of match_f32_kernel on the whole chip (256 CUs x 2).
-constexpr int kF32Slots = 512;
+// Resident blocks of match_f32_kernel and match_bf16_kernel on the whole
+// chip (256 CUs x 2).
+constexpr int kSlots = 512;
 
-// Number of K splits that best fills the chip's resident blocks, with each
-// split at least 1024 values of P long.  Only launches of under half a
-// round of tiles are split: blocks are dispatched dynamically, so a partial
-// last round costs less than the partial tiles' extra traffic (measured on
-// 1,264 tiles of K = 16,384: unsplit 5.8 ms, two splits 6.7 ms).
-int match_f32_splits(int64_t M, int64_t N, int64_t P) {
+// K splits of a launch of 128 x 128 tiles: enough to give every resident
+// block a share, each at least 512 values of P long (16 FP32 or 8 BF16 K
+// steps).  Only launches of under half a round of tiles are split: blocks are
+// dispatched dynamically, so a partial last round costs less than the
+// partial tiles' extra traffic (measured on 1,264 tiles of K = 16,384:
+// unsplit 5.8 ms, two splits 6.7 ms).
+static int tile_splits(int64_t M, int64_t N, int64_t P) {
   const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  if (2 * tiles >= kF32Slots) return 1;
-  int best = 1;
-  double best_eff = 0.0;
-  for (int s = 1; s <= 4; ++s) {
-    if (s > 1 && P / s < 1024) break;
-    const int64_t units = tiles * s;
-    const int64_t rounds = (units + kF32Slots - 1) / kF32Slots;
-    const double eff = (double)units / (double)(rounds * kF32Slots);
-    if (eff > best_eff + 0.02) {
-      best_eff = eff;
-      best = s;
-    }
-  }
-  return best;
+  if (tiles == 0 || 2 * tiles >= kSlots) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kSlots / tiles, P / 512));
+}
+
+static size_t partial_bytes(int64_t M, int64_t N, int64_t P) {
+  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+  const int s = tile_splits(M, N, P);
+  return s > 1 ? (size_t)tiles * s * kBM * kBN * sizeof(float) : 0;
 }
 
 size_t match_f32_workspace_bytes(int64_t M, int64_t N, int64_t P) {
-  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  const int s = match_f32_splits(M, N, P);
-  size_t b = (size_t)N * sizeof(unsigned long long);
-  b = (b + 255) & ~(size_t)255;
-  if (s > 1) {
-    b += (size_t)tiles * sizeof(unsigned);
-    b = (b + 255) & ~(size_t)255;
-    b += (size_t)tiles * s * kBM * kBN * sizeof(float);
-  }
-  return b;
+  return (((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255) + partial_bytes(M, N, P);
 }
 
 hipError_t launch_match_f32(const float *S, const float *D, const float *sn, const float *dn,
@@ -307,28 +322,20 @@ hipError_t launch_match_f32(const float *S, const float *D, const float *sn, con
                             hipStream_t s) {
   const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  const int splits = match_f32_splits(M, N, P);
+  const int splits = tile_splits(M, N, P);
   const int64_t blocks = tiles * splits;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  // K chunk: a multiple of the K step (and of 4 for the vector loads)
+  // K chunk: a multiple of the K step
   int64_t kchunk = (P + splits - 1) / splits;
   kchunk = (kchunk + kBK - 1) / kBK * kBK;
-  const int vec = (P % 4 == 0) && al16(S) && al16(D);
   char *ws = static_cast<char *>(workspace);
   auto *keys = reinterpret_cast<unsigned long long *>(ws);
-  size_t off = ((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255;
-  unsigned *counters = nullptr;
-  float *partials = nullptr;
-  if (splits > 1) {
-    counters = reinterpret_cast<unsigned *>(ws + off);
-    off = (off + (size_t)tiles * sizeof(unsigned) + 255) & ~(size_t)255;
-    partials = reinterpret_cast<float *>(ws + off);
-    hipError_t e = launch_fill_zero(counters, (size_t)tiles * sizeof(unsigned), s);
-    if (e != hipSuccess) return e;
-  }
+  float *partials = reinterpret_cast<float *>(ws + (((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255));
   hipLaunchKernelGGL(match_f32_kernel, dim3((unsigned)blocks), dim3(kF32Threads), 0, s, S, D, sn, dn, M, N,
-                     P, (uint32_t)m_offset, keys, tiles_m, tiles_n, vec, splits, kchunk, partials,
-                     counters);
+                     P, (uint32_t)m_offset, keys, tiles_m, tiles_n, splits, kchunk, partials);
+  if (splits > 1)
+    hipLaunchKernelGGL(reduce_f32_kernel, dim3((unsigned)(tiles * (kBN / kRedCols))), dim3(256), 0, s,
+                       partials, splits, sn, dn, M, N, (uint32_t)m_offset, tiles_n, keys);
   return hipGetLastError();
 }
 
@@ -336,14 +343,20 @@ hipError_t launch_match_f32(const float *S, const float *D, const float *sn, con
 constexpr int kBKH = 64;          // bf16 values of P per K step
 constexpr int kLdH = kBKH + 8;    // LDS row stride (bf16 values)
 
+// Eight consecutive values of a row of length ld, zero beyond row `rows` or
+// column `kend`; whole groups in one load at whatever alignment the row has.
 __device__ inline uint4 load_row8h(const uint16_t *__restrict__ X, int64_t rows, int64_t r,
-                                   int64_t P, int64_t k, bool vec) {
-  if (r >= rows) return make_uint4(0u, 0u, 0u, 0u);
-  const uint16_t *p = X + r * P + k;
-  if (vec) return k < P ? *reinterpret_cast<const uint4 *>(p) : make_uint4(0u, 0u, 0u, 0u);
+                                   int64_t kend, int64_t k, int64_t ld) {
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (r >= rows) return v;
+  const uint16_t *p = X + r * ld + k;
+  if (k + 8 <= kend) {
+    __builtin_memcpy(&v, p, 16);
+    return v;
+  }
   uint32_t h[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = k + e < P ? p[e] : 0u;
+  for (int e = 0; e < 8; ++e) h[e] = k + e < kend ? p[e] : 0u;
   return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
@@ -387,7 +400,7 @@ size_t match_bf16_candidate_bytes(int64_t M, int64_t N) {
 __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
     const uint16_t *__restrict__ S, const uint16_t *__restrict__ D, const float *__restrict__ sn,
     const float *__restrict__ dn, int64_t M, int64_t N, int64_t P, uint32_t *__restrict__ cand,
-    int tiles_m, int tiles_n, int vec) {
+    int tiles_m, int tiles_n, int splits, int64_t kchunk, float *__restrict__ partials) {
   constexpr int kSeg = kBKH / 8;           // 16-byte segments per row and step
   constexpr int kLoads = kBM * kSeg / 256; // segments per thread and operand
   __shared__ __attribute__((aligned(16))) uint16_t As[kBM * kLdH];
@@ -396,18 +409,19 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
   __shared__ uint32_t red[2][kBN][8];
 
   int tm, tn, split;
-  tile_of_block(tiles_m, tiles_n, 1, tm, tn, split);
+  tile_of_block(tiles_m, tiles_n, splits, tm, tn, split);
   const int64_t row0 = (int64_t)tm * kBM, col0 = (int64_t)tn * kBN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, lr = lane & 31, lh = lane >> 5;
+  const int64_t kbeg = (int64_t)split * kchunk, kend = min(P, kbeg + kchunk);
 
   uint4 ra[kLoads], rb[kLoads];
   auto gload = [&](int64_t k0) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int id = tid + 256 * i, r = id / kSeg, c = (id % kSeg) * 8;
-      ra[i] = load_row8h(S, M, row0 + r, P, k0 + c, vec);
-      rb[i] = load_row8h(D, N, col0 + r, P, k0 + c, vec);
+      ra[i] = load_row8h(S, M, row0 + r, kend, k0 + c, P);
+      rb[i] = load_row8h(D, N, col0 + r, kend, k0 + c, P);
     }
   };
 
@@ -419,8 +433,8 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  gload(0);
-  for (int64_t k0 = 0; k0 < P; k0 += kBKH) {
+  gload(kbeg);
+  for (int64_t k0 = kbeg; k0 < kend; k0 += kBKH) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
@@ -429,7 +443,7 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
       *reinterpret_cast<uint4 *>(&Bs[r * kLdH + c]) = rb[i];
     }
     __syncthreads();
-    if (k0 + kBKH < P) gload(k0 + kBKH);
+    if (k0 + kBKH < kend) gload(k0 + kBKH);
 #pragma unroll
     for (int kk = 0; kk < kBKH / 16; ++kk) {
       bf16x8 a[2], b[2];
@@ -447,6 +461,18 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
     }
   }
 
+  if (splits > 1) {
+    float *mine = partials + ((int64_t)(tm * tiles_n + tn) * splits + split) * (kBM * kBN);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          mine[(wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * kBN + wn * 64 + j * 32 + lr] =
+              acc[i][j][r];
+    return;
+  }
   if (tid < kBM) {
     sns[tid] = row0 + tid < M ? sn[row0 + tid] : 0.f;
   } else {
@@ -488,6 +514,44 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
 #pragma unroll
     for (int s = 0; s < 8; ++s) insert8(top, red[1][tid][s]);
     uint4 *dst = reinterpret_cast<uint4 *>(cand + ((int64_t)tm * N + col0 + tid) * 8);
+    dst[0] = make_uint4(top[0], top[1], top[2], top[3]);
+    dst[1] = make_uint4(top[4], top[5], top[6], top[7]);
+  }
+}
+
+// Epilogue of a split launch: per-tile column top-8 of the summed partials
+// (threads as in reduce_f32_kernel).
+__global__ __launch_bounds__(256) void reduce_bf16_kernel(
+    const float *__restrict__ partials, int splits, const float *__restrict__ sn,
+    const float *__restrict__ dn, int64_t M, int64_t N, int tiles_n, uint32_t *__restrict__ cand) {
+  constexpr int kGroups = 256 / kRedCols;
+  __shared__ uint32_t red[kGroups][kRedCols][9];
+  const int tile = blockIdx.x / (kBN / kRedCols), c0 = (blockIdx.x % (kBN / kRedCols)) * kRedCols;
+  const int cl = threadIdx.x & (kRedCols - 1), rg = threadIdx.x / kRedCols;
+  const int tm = tile / tiles_n;
+  const int64_t row0 = (int64_t)tm * kBM, n = (int64_t)(tile % tiles_n) * kBN + c0 + cl;
+  const float *part = partials + (int64_t)tile * splits * (kBM * kBN);
+  uint32_t top[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) top[s] = ~0u;
+  if (n < N) {
+    const float dnn = dn[n];
+#pragma unroll 4
+    for (int j = 0; j < kRedRows; ++j) {
+      const int row = rg * kRedRows + j;
+      if (row0 + row >= M) break;
+      const float b = fmaf(-2.0f, split_sum(part, splits, row, c0 + cl), sn[row0 + row] + dnn);
+      insert8(top, (float_key(b) & ~127u) | (uint32_t)row);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) red[rg][cl][s] = top[s];
+  __syncthreads();
+  if (rg == 0 && n < N) {
+    for (int k = 1; k < kGroups; ++k)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) insert8(top, red[k][cl][s]);
+    uint4 *dst = reinterpret_cast<uint4 *>(cand + ((int64_t)tm * N + n) * 8);
     dst[0] = make_uint4(top[0], top[1], top[2], top[3]);
     dst[1] = make_uint4(top[4], top[5], top[6], top[7]);
   }
@@ -685,10 +749,11 @@ __global__ __launch_bounds__(512, 1) void match_bf16_big_kernel(
   }
 }
 
+size_t match_bf16_partial_bytes(int64_t M, int64_t N, int64_t P) { return partial_bytes(M, N, P); }
+
 hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *sn,
                              const float *dn, int64_t M, int64_t N, int64_t P, uint32_t *cand,
-                             hipStream_t s) {
-  const int vec = (P % 8 == 0) && al16(S) && al16(D);
+                             float *partials, hipStream_t s) {
   if (match_bf16_tile_rows(M, N, P, S, D) == 256) {
     const int tiles_m = (int)((M + kBM2 - 1) / kBM2), tiles_n = (int)((N + kBN2 - 1) / kBN2);
     const int64_t blocks = (int64_t)tiles_m * tiles_n;
@@ -698,10 +763,15 @@ hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *
     return hipGetLastError();
   }
   const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-  const int64_t blocks = (int64_t)tiles_m * tiles_n;
+  const int splits = tile_splits(M, N, P);
+  const int64_t tiles = (int64_t)tiles_m * tiles_n, blocks = tiles * splits;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  const int64_t kchunk = ((P + splits - 1) / splits + kBKH - 1) / kBKH * kBKH;
   hipLaunchKernelGGL(match_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, S, D, sn, dn, M,
-                     N, P, cand, tiles_m, tiles_n, vec);
+                     N, P, cand, tiles_m, tiles_n, splits, kchunk, partials);
+  if (splits > 1)
+    hipLaunchKernelGGL(reduce_bf16_kernel, dim3((unsigned)(tiles * (kBN / kRedCols))), dim3(256), 0, s,
+                       partials, splits, sn, dn, M, N, tiles_n, cand);
   return hipGetLastError();
 }
 
@@ -741,26 +811,26 @@ __device__ inline float upper_sqrt_rescored(float d, float g_run) {
   return sqrtf(d * (1.0f + 2.0f * g_run)) * kHi;
 }
 
-// Sum over p of (s_p - d_p)^2 for one lane's share of a row (float32).
+// Sum over p of (s_p - d_p)^2 for one lane's share of a row (float32): whole
+// quads at whatever alignment the rows have, then the last P % 4 values.
 __device__ inline float direct_part(const float *__restrict__ srow, const float *__restrict__ drow,
-                                    int64_t P, int lane, int vec) {
+                                    int64_t P, int lane) {
   float acc = 0.f;
-  if (vec) {
-    const float4 *s4 = reinterpret_cast<const float4 *>(srow);
-    const float4 *d4 = reinterpret_cast<const float4 *>(drow);
-    for (int64_t q = lane; q < P / 4; q += 64) {
-      const float4 a = s4[q], b = d4[q];
-      float t;
-      t = a.x - b.x; acc = fmaf(t, t, acc);
-      t = a.y - b.y; acc = fmaf(t, t, acc);
-      t = a.z - b.z; acc = fmaf(t, t, acc);
-      t = a.w - b.w; acc = fmaf(t, t, acc);
-    }
-  } else {
-    for (int64_t p = lane; p < P; p += 64) {
-      const float t = srow[p] - drow[p];
-      acc = fmaf(t, t, acc);
-    }
+#pragma unroll 2
+  for (int64_t q = lane; q < P / 4; q += 64) {
+    float4 a, b;
+    __builtin_memcpy(&a, srow + 4 * q, 16);
+    __builtin_memcpy(&b, drow + 4 * q, 16);
+    float t;
+    t = a.x - b.x; acc = fmaf(t, t, acc);
+    t = a.y - b.y; acc = fmaf(t, t, acc);
+    t = a.z - b.z; acc = fmaf(t, t, acc);
+    t = a.w - b.w; acc = fmaf(t, t, acc);
+  }
+  const int64_t p = (P & ~(int64_t)3) + lane;
+  if (p < P) {
+    const float t = srow[p] - drow[p];
+    acc = fmaf(t, t, acc);
   }
   return acc;
 }
@@ -771,10 +841,12 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// Chunk maxima the certificate needs: max_m |s^_m| and max_m e_m.
+// Chunk maxima the certificate needs: max_m |s^_m| and max_m e_m; clears the
+// fallback count.
 __global__ __launch_bounds__(1024) void chunk_stats_kernel(const float *__restrict__ sn,
                                                            const float *__restrict__ se, int64_t M,
-                                                           float *__restrict__ stats) {
+                                                           float *__restrict__ stats,
+                                                           unsigned *__restrict__ count) {
   __shared__ float sh[2][1024];
   float a = 0.f, b = 0.f;
   for (int64_t m = threadIdx.x; m < M; m += 1024) {
@@ -794,6 +866,7 @@ __global__ __launch_bounds__(1024) void chunk_stats_kernel(const float *__restri
   if (threadIdx.x == 0) {
     stats[0] = sh[0][0];
     stats[1] = sh[1][0];
+    *count = 0u;
   }
 }
 
@@ -817,7 +890,7 @@ __global__ __launch_bounds__(256) void rescore_kernel(
     const float *__restrict__ de, const float *__restrict__ stats, CertBounds cb,
     int32_t *__restrict__ best_idx, float *__restrict__ best_dist, int32_t *__restrict__ flags,
     unsigned *__restrict__ fb_count, int32_t *__restrict__ fb_list,
-    unsigned long long *__restrict__ fb_keys, int vec) {
+    unsigned long long *__restrict__ fb_keys) {
   const int lane = threadIdx.x & 63;
   const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (n >= N) return;
@@ -874,7 +947,7 @@ __global__ __launch_bounds__(256) void rescore_kernel(
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       if (take[s]) {   // wavefront-uniform
-        const float d = wave_sum(direct_part(S32 + (int64_t)mi[s] * P, drow, P, lane, vec));
+        const float d = wave_sum(direct_part(S32 + (int64_t)mi[s] * P, drow, P, lane));
         const unsigned long long key =
             ((unsigned long long)float_key(d) << 32) | (uint32_t)(m_offset + (uint32_t)mi[s]);
         best = key < best ? key : best;
@@ -913,7 +986,7 @@ __global__ __launch_bounds__(256) void rescore_kernel(
 __global__ __launch_bounds__(256) void fallback_kernel(
     const float *__restrict__ S32, const float *__restrict__ D32, int64_t M, int64_t P,
     uint32_t m_offset, const unsigned *__restrict__ fb_count, const int32_t *__restrict__ fb_list,
-    unsigned long long *__restrict__ fb_keys, int vec) {
+    unsigned long long *__restrict__ fb_keys) {
   __shared__ unsigned long long red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t slabs = (M + 63) / 64;
@@ -926,7 +999,7 @@ __global__ __launch_bounds__(256) void fallback_kernel(
     for (int r = 0; r < 16; ++r) {
       const int64_t m = slab * 64 + wave * 16 + r;
       if (m >= M) break;   // wavefront-uniform
-      const float d = wave_sum(direct_part(S32 + m * P, drow, P, lane, vec));
+      const float d = wave_sum(direct_part(S32 + m * P, drow, P, lane));
       const unsigned long long key =
           ((unsigned long long)float_key(d) << 32) | (uint32_t)(m_offset + (uint32_t)m);
       best = key < best ? key : best;
@@ -968,7 +1041,6 @@ hipError_t launch_rescore(const uint32_t *cand, int tile_rows, int64_t M, int64_
                           float *best_dist, int32_t *flags, void *scratch, hipStream_t s) {
   const int tr = tile_rows;
   const int tiles_m = (int)((M + tr - 1) / tr);
-  const int vec = (P % 4 == 0) && al16(S32) && al16(D32);
   char *w = static_cast<char *>(scratch);
   float *stats = reinterpret_cast<float *>(w);
   unsigned *count = reinterpret_cast<unsigned *>(w + 16);
@@ -978,14 +1050,12 @@ hipError_t launch_rescore(const uint32_t *cand, int tile_rows, int64_t M, int64_
   cb.g_acc = (float)gamma_of((double)(P / 16) + 8.0, 0x1p-23);
   cb.g_n = (float)gamma_of((double)(P / 256) + 24.0, 0x1p-24);
   cb.g_run = (float)gamma_of((double)(P / 64) + 16.0, 0x1p-24);
-  hipError_t e = launch_fill_zero(count, 4, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_stats_kernel, dim3(1), dim3(1024), 0, s, sn, se, M, stats);
+  hipLaunchKernelGGL(chunk_stats_kernel, dim3(1), dim3(1024), 0, s, sn, se, M, stats, count);
   hipLaunchKernelGGL(rescore_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s, cand, tiles_m,
                      tr, M, N, P, (uint32_t)m_offset, S32, D32, sn, dn, se, de, stats, cb, best_idx,
-                     best_dist, flags, count, list, keys, vec);
+                     best_dist, flags, count, list, keys);
   hipLaunchKernelGGL(fallback_kernel, dim3(1024), dim3(256), 0, s, S32, D32, M, P,
-                     (uint32_t)m_offset, count, list, keys, vec);
+                     (uint32_t)m_offset, count, list, keys);
   hipLaunchKernelGGL(fallback_unpack_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s,
                      count, list, keys, best_idx, best_dist);
   return hipGetLastError();

@@ -1,0 +1,50 @@
+"""Matcher launches that split K over blocks (few tiles) and rows at every
+alignment (row lengths that are not a multiple of 4 or 8), against the
+oracle's float64 distances.  Images are Poisson counts of picked rows, so
+every image is decided; the distance bounds are the documented chains (FP32:
+36 + ceil(P/32) roundings of the expanded form, BF16: P/64 + 16 of the direct
+sum)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2109_05339_amd as spfel
+from oracle import match as om
+from tests._common import DEV, gpu, host
+
+pytestmark = pytest.mark.gpu
+
+
+# one tile at 1 and at 128 rows and images, one past, P below one split's
+# length (unsplit), at and just past two, ragged by 1, 2 and 7, more splits
+# than whole K steps per split divide evenly, and a launch past half a round
+# of tiles (unsplit)
+@pytest.mark.parametrize("M,N,P", [
+    (1, 1, 1024), (3, 2, 1023), (128, 128, 1025), (129, 127, 1030), (257, 130, 5121),
+    (300, 40, 8199), (64, 200, 16390), (40, 9, 511), (2100, 2050, 700),
+])
+@pytest.mark.parametrize("mode", [spfel.MATCH_FP32, spfel.MATCH_BF16_RESCORE8])
+def test_split_and_ragged_launches(mode, M, N, P):
+    g = np.random.default_rng(M + N + P)
+    S = g.gamma(2.0, 15.0, (M, P)).astype(np.float32)
+    pick = g.integers(0, M, N)
+    D = g.poisson(S[pick]).astype(np.float32)
+    St, Dt = gpu(S), gpu(D)
+    bi, bd = spfel.new_best(N, DEV)
+    S64, D64 = S.astype(np.float64), D.astype(np.float64)
+    ex = om.distances_expanded(S64, D64)
+    cols = np.arange(N)
+    if mode == spfel.MATCH_FP32:
+        spfel.match(St, spfel.row_norm2(St), Dt, spfel.row_norm2(Dt), bi, bd)
+        absdot = np.abs(S64) @ np.abs(D64).T
+        E = om.fp32_distance_bound((S64 ** 2).sum(1)[:, None], (D64 ** 2).sum(1)[None, :], absdot,
+                                   36 + -(-P // 32))
+    else:
+        im = spfel.ImagesBF16(Dt, centre=gpu(om.centre_rounded_mean(D)))
+        spfel.match_bf16(St, im, bi, bd)
+        E = 2 * om.gamma(P // 64 + 16) * ex + 1e-30
+    bi, bd = host(bi), host(bd)
+    am = om.argmin_first(ex)
+    assert np.array_equal(am, pick)
+    assert np.array_equal(bi, am)
+    assert np.all(np.abs(bd - ex[am, cols]) <= E[am, cols])
