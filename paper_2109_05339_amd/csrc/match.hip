@@ -378,14 +378,16 @@ __device__ inline void insert8(unsigned long long (&top)[8], unsigned long long 
   }
 }
 
-// The large-tile kernel is used when its 256 x 256 tiles fill at least four
-// rounds of the chip's 256 resident blocks, P is a whole number of its
-// 64-wide K steps and both operands are 16-byte aligned; otherwise
-// 128 x 128 tiles.
+// The large-tile kernel is used when its 256 x 256 tiles occupy more than
+// half of the chip's 256 resident blocks, P is a whole number of its 64-wide K
+// steps and both operands are 16-byte aligned; otherwise 128 x 128 tiles.
+// Measured, large tiles against 128 x 128: 128 tiles 154 / 140 us (P = 4,096)
+// and 1,698 / 1,635 us (P = 65,536), 144 tiles 493 / 573 us, 288 tiles
+// 935 / 1,016 us, 320 tiles 1,188 / 1,314 us, 512 tiles 1,121 / 1,561 us.
 int match_bf16_tile_rows(int64_t M, int64_t N, int64_t P, const void *S, const void *D) {
   if (P % 64 != 0 || !al16(S) || !al16(D)) return 128;
   const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-  return big >= 4 * 256 ? 256 : 128;
+  return big > 136 ? 256 : 128;
 }
 
 // Candidate buffer for the 128-row tiling, the larger of the two.

@@ -1,7 +1,7 @@
 """Matcher launches that split K over blocks (few tiles) and rows at every
 alignment (row lengths that are not a multiple of 4 or 8), against the
 oracle's float64 distances.  Images are Poisson counts of picked rows, so
-every image is decided; the distance bounds are the documented chains (FP32:
+almost every image is decided; the distance bounds are the documented chains (FP32:
 36 + ceil(P/32) roundings of the expanded form, BF16: P/64 + 16 of the direct
 sum)."""
 import numpy as np
@@ -17,18 +17,18 @@ pytestmark = pytest.mark.gpu
 
 # one tile at 1 and at 128 rows and images, one past, P below one split's
 # length (unsplit), at and just past two, ragged by 1, 2 and 7, more splits
-# than whole K steps per split divide evenly, and a launch past half a round
-# of tiles (unsplit)
+# than whole K steps per split divide evenly, a launch past half a round of
+# 128-row tiles (unsplit), and launches of 256-row tiles (144 of
+# them) and just below (136: 128-row tiles)
 @pytest.mark.parametrize("M,N,P", [
     (1, 1, 1024), (3, 2, 1023), (128, 128, 1025), (129, 127, 1030), (257, 130, 5121),
-    (300, 40, 8199), (64, 200, 16390), (40, 9, 511), (2100, 2050, 700),
+    (300, 40, 8199), (64, 200, 16390), (40, 9, 511), (2100, 2050, 700), (300, 17400, 64), (4400, 1990, 64),
 ])
 @pytest.mark.parametrize("mode", [spfel.MATCH_FP32, spfel.MATCH_BF16_RESCORE8])
 def test_split_and_ragged_launches(mode, M, N, P):
     g = np.random.default_rng(M + N + P)
     S = g.gamma(2.0, 15.0, (M, P)).astype(np.float32)
-    pick = g.integers(0, M, N)
-    D = g.poisson(S[pick]).astype(np.float32)
+    D = g.poisson(S[g.integers(0, M, N)]).astype(np.float32)
     St, Dt = gpu(S), gpu(D)
     bi, bd = spfel.new_best(N, DEV)
     S64, D64 = S.astype(np.float64), D.astype(np.float64)
@@ -45,6 +45,11 @@ def test_split_and_ragged_launches(mode, M, N, P):
         E = 2 * om.gamma(P // 64 + 16) * ex + 1e-30
     bi, bd = host(bi), host(bd)
     am = om.argmin_first(ex)
-    assert np.array_equal(am, pick)
-    assert np.array_equal(bi, am)
+    # images whose exact gap exceeds the bounds (all, but for very short rows)
+    order = np.argpartition(ex, min(1, M - 1), axis=0) if M > 1 else np.zeros((2, N), int)
+    second = np.where(order[0] == am, order[1], order[0]) if M > 1 else am
+    decided = ex[second, cols] - ex[am, cols] > E[second, cols] + E[am, cols] if M > 1 else np.ones(N, bool)
+    assert decided.mean() >= 0.99
+    assert np.array_equal(bi[decided], am[decided])
+    am = bi
     assert np.all(np.abs(bd - ex[am, cols]) <= E[am, cols])
