@@ -50,14 +50,76 @@ __device__ inline void load_cells(const T *__restrict__ u, uint32_t o, T (&v)[W]
     for (int c = kWhole; c < W; ++c) v[c] = u[o + c];
 }
 
-// Per-point gather for points given with the call: a row of the support is W
-// consecutive cells (one that crosses the grid's end is read cell by cell).
-// What bounds it is the traffic of those reads from L2 (the points of the
-// wavefronts on a CU reach far more cells than the L1 holds), so they are as
-// wide as they can be, and the planes are not unrolled: with 8-byte loads and
-// everything unrolled the complex kernel held 451 registers, one wavefront
-// per SIMD, and took 547 us on 200 x 10,089 points of a 130^3 grid; 385 us
-// here (603 us with 8-byte loads).
+// The support of one point, read from the grid: base is the first cell (in
+// [0, n_f), storage order) along each axis.  A row of the support is W
+// consecutive cells; one that crosses the grid's end is read cell by cell.
+// The planes are not unrolled: with everything unrolled the complex form held
+// 451 registers, one wavefront per SIMD.
+template <int W, bool CPLX, class T>
+__device__ inline void gather_support(const T *__restrict__ u, int nf, const int (&base)[3],
+                                      const float (&w0)[W], const float (&w1)[W],
+                                      const float (&w2)[W], float &sr, float &si) {
+  uint32_t o1[W];   // row offsets of axis 1 (n_f <= 1022: cells index in 32 bits)
+#pragma unroll
+  for (int b = 0; b < W; ++b) {
+    int i1 = base[1] + b;
+    i1 -= i1 >= nf ? nf : 0;
+    o1[b] = (uint32_t)(i1 * nf);
+  }
+  const uint32_t nf2 = (uint32_t)nf * nf;
+  sr = si = 0.f;
+  auto planes = [&](auto contiguous) {
+#pragma unroll 1
+    for (int a = 0; a < W; ++a) {
+      int i0 = base[0] + a;
+      i0 -= i0 >= nf ? nf : 0;
+      const uint32_t plane = (uint32_t)i0 * nf2;
+      float pr = 0.f, pi = 0.f;
+#pragma unroll
+      for (int b = 0; b < W; ++b) {
+        T v[W];
+        if constexpr (decltype(contiguous)::value) {
+          load_cells<W>(u, plane + o1[b] + (uint32_t)base[2], v);
+        } else {
+#pragma unroll
+          for (int c = 0; c < W; ++c) {
+            int i2 = base[2] + c;
+            i2 -= i2 >= nf ? nf : 0;
+            v[c] = u[plane + o1[b] + (uint32_t)i2];
+          }
+        }
+        float rr = 0.f, ri = 0.f;
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+          if constexpr (CPLX) {
+            rr = fmaf(w2[c], v[c].x, rr);
+            ri = fmaf(w2[c], v[c].y, ri);
+          } else {
+            rr = fmaf(w2[c], v[c], rr);
+          }
+        }
+        pr = fmaf(w1[b], rr, pr);
+        if (CPLX) pi = fmaf(w1[b], ri, pi);
+      }
+      // psi0 of plane a (the planes are not unrolled)
+      float wa = w0[0];
+#pragma unroll
+      for (int e = 1; e < W; ++e) wa = a == e ? w0[e] : wa;
+      sr = fmaf(wa, pr, sr);
+      if (CPLX) si = fmaf(wa, pi, si);
+    }
+  };
+  if (base[2] + W <= nf)
+    planes(std::true_type{});
+  else
+    planes(std::false_type{});
+}
+
+// Per-point gather for points given with the call.  What bounds it is the
+// traffic of the reads from L2 (the points of the wavefronts on a CU reach far
+// more cells than the L1 holds), so they are as wide as they can be: 200 x
+// 10,089 complex points of a 130^3 grid took 547 us with 8-byte loads and
+// unrolled planes, 385 us here (603 us with 8-byte loads).
 template <int W, bool CPLX>
 __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
     const void *__restrict__ u_, int nf, float beta, const double *__restrict__ rot, int64_t M,
@@ -85,61 +147,7 @@ __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
     es_weights<W>(frac[0], beta, w0);
     es_weights<W>(frac[1], beta, w1);
     es_weights<W>(frac[2], beta, w2);
-    const T *u = static_cast<const T *>(u_);
-    uint32_t o1[W];   // row offsets of axis 1 (n_f <= 1022: cells index in 32 bits)
-#pragma unroll
-    for (int b = 0; b < W; ++b) {
-      int i1 = base[1] + b;
-      i1 -= i1 >= nf ? nf : 0;
-      o1[b] = (uint32_t)(i1 * nf);
-    }
-    const uint32_t nf2 = (uint32_t)nf * nf;
-    sr = si = 0.f;
-    auto planes = [&](auto contiguous) {
-#pragma unroll 1
-      for (int a = 0; a < W; ++a) {
-        int i0 = base[0] + a;
-        i0 -= i0 >= nf ? nf : 0;
-        const uint32_t plane = (uint32_t)i0 * nf2;
-        float pr = 0.f, pi = 0.f;
-#pragma unroll
-        for (int b = 0; b < W; ++b) {
-          T v[W];
-          if constexpr (decltype(contiguous)::value) {
-            load_cells<W>(u, plane + o1[b] + (uint32_t)base[2], v);
-          } else {
-#pragma unroll
-            for (int c = 0; c < W; ++c) {
-              int i2 = base[2] + c;
-              i2 -= i2 >= nf ? nf : 0;
-              v[c] = u[plane + o1[b] + (uint32_t)i2];
-            }
-          }
-          float rr = 0.f, ri = 0.f;
-#pragma unroll
-          for (int c = 0; c < W; ++c) {
-            if constexpr (CPLX) {
-              rr = fmaf(w2[c], v[c].x, rr);
-              ri = fmaf(w2[c], v[c].y, ri);
-            } else {
-              rr = fmaf(w2[c], v[c], rr);
-            }
-          }
-          pr = fmaf(w1[b], rr, pr);
-          if (CPLX) pi = fmaf(w1[b], ri, pi);
-        }
-        // psi0 of plane a (the planes are not unrolled)
-        float wa = w0[0];
-#pragma unroll
-        for (int e = 1; e < W; ++e) wa = a == e ? w0[e] : wa;
-        sr = fmaf(wa, pr, sr);
-        if (CPLX) si = fmaf(wa, pi, si);
-      }
-    };
-    if (base[2] + W <= nf)
-      planes(std::true_type{});
-    else
-      planes(std::false_type{});
+    gather_support<W, CPLX>(static_cast<const T *>(u_), nf, base, w0, w1, w2, sr, si);
   }
   if (!out_) return;
   if constexpr (CPLX)
@@ -151,11 +159,15 @@ __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
 // ---------------------------------------------------------------------------
 // Tiled interpolation over the registered detector.  One block of kTile
 // threads takes one orientation and one detector tile (kTile consecutive
-// points of the Hilbert-ordered template, hence a compact patch): the rotated points' support
-// cells span a small axis-aligned brick of the fine grid, which the block
-// stages in LDS with coalesced row reads; the w^3 gather then reads LDS
-// instead of L1/L2.  A brick larger than the LDS budget (possible only for
-// unusually spread tiles) makes the block gather from global memory.
+// points of the Hilbert-ordered template, hence a compact patch): the rotated
+// points' support cells span a small axis-aligned brick of the fine grid,
+// which the block stages in LDS with coalesced row reads; the w^3 gather then
+// reads LDS instead of L1/L2.  A tile whose brick exceeds the LDS budget (a
+// detector that is coarse against the grid) is staged in parts.
+//
+// What bounds it (REAL, w = 6, 65^3 model, 2,048 images of 128^2 pixels,
+// 0.92 ms): the LDS is busy 93% of the time, 43% of that with bank conflicts of
+// the gather, and the vector units three quarters of it.
 // LDS budget of a brick: 29 KB of float (5 blocks per CU, the kernel then
 // fits in 81 registers) or 64 KB of float2 cells.
 template <bool CPLX>
@@ -176,6 +188,39 @@ __device__ inline int wrap_mod(int v, int n) {
     v += v < 0 ? n : 0;
   }
   return v;
+}
+
+// The brick around the support cells of `gw` wavefronts from `first` on:
+// lowest support origin and extent per axis, from the wavefronts' origin
+// ranges (red: minima, maxima).  (Uniform, but left in vector registers: read
+// out as scalars they cost 2% of the kernel.)
+constexpr int kNone = 0x7fffffff;   // minimum of no points
+template <int W, int VEC>
+struct BrickBox {
+  int mn[3], e[3];
+  bool any;
+  // whether its rows, in whole 16-byte segments, fit into `cap` cells (those of
+  // no points do)
+  __device__ bool fits(int cap) const {
+    return e[0] <= 64 && e[1] <= 64 && e[2] <= 64 &&
+           e[0] * e[1] * ((e[2] + VEC - 1) / VEC * VEC) <= cap;
+  }
+};
+template <int W, int VEC>
+__device__ inline BrickBox<W, VEC> brick_of(const int (*red)[6], int first, int gw) {
+  BrickBox<W, VEC> b;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    int lo = kNone, hi = -kNone;
+    for (int w = first; w < first + gw; ++w) {
+      lo = min(lo, red[w][d]);
+      hi = max(hi, red[w][3 + d]);
+    }
+    b.mn[d] = lo;
+    b.any = b.mn[d] != kNone;
+    b.e[d] = b.any ? hi - b.mn[d] + W : 0;
+  }
+  return b;
 }
 
 template <int W, bool CPLX>
@@ -217,237 +262,230 @@ __global__ __launch_bounds__(kTile, CPLX ? 4 : 5) void interp_tiled_kernel(
   int mn[3], mx[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    mn[d] = valid ? l0[d] : 0x7fffffff;
-    mx[d] = valid ? l0[d] : -0x7fffffff;
+    mn[d] = valid ? l0[d] : kNone;
+    mx[d] = valid ? l0[d] : -kNone;
   }
   block_minmax3(mn, mx, red);
-  const bool any = mn[0] <= mx[0];
-  const int e0 = mx[0] - mn[0] + W, e1 = mx[1] - mn[1] + W, e2 = mx[2] - mn[2] + W;
-  // Brick layout: cell (x0, x1, x2) at x0 * s0 + x1 * p2 + x2, with the row
-  // pitch p2 >= p4 (e2 rounded up to whole 16-byte segments, so a segment
-  // store never spills into the next row) and the plane stride
-  // s0 >= e1 * p2.  The small paddings are chosen per block: a wavefront's
-  // 64 lanes read 64 cells at a common offset from their support origins,
-  // so the LDS bank conflicts of every gather read are those of the lanes'
-  // origin addresses.  The first wavefront scores each candidate layout by
-  // letting every lane write its origin address into a table slot named by
-  // the address's bank group (one table per LDS pass of lanes) and read the
-  // slot back: a lane that finds another address there shares its banks
-  // with a different cell in its pass.  The candidate with the fewest such
-  // lanes wins (ties: the first); the other wavefronts' patches lie next to
-  // the first's, under the same rotation, and share its choice.  Eight
-  // candidates (row paddings 0-3, plane offsets 0 and 2) choose as well as
-  // sixteen (offsets 0-3) at half the probe's cost.
   constexpr int kVec = 16 / (int)sizeof(T);
-  const int nseg = (e2 + kVec - 1) / kVec;
-  const int p4 = nseg * kVec;
-  const bool use_lds = any && e0 <= 64 && e1 <= 64 && e2 <= 64 && e0 * e1 * p4 <= kCap;
-  const bool choose = use_lds && e0 * (e1 * (p4 + 3) + 2) <= kCap;
-  if (use_lds && threadIdx.x < 64) {
-    // fine-grid offsets of every brick plane, row and column, wrapped once
-    // per block (n_f <= 1022, so n_f^3 cells index in 32 bits)
-    const int t = threadIdx.x, half = nf >> 1;
-    if (t < e0) wrap[0][t] = wrap_mod(mn[0] + t + half, nf) * nf * nf;
-    if (t < e1) wrap[1][t] = wrap_mod(mn[1] + t + half, nf) * nf;
-    if (t < e2) wrap[2][t] = wrap_mod(mn[2] + t + half, nf);
-    if (choose) {
-      // candidate c = 2 pe + d / 2: p2 = p4 + pe, s0 = e1 p2 + d (d = 0, 2),
-      // so the origin address is row * (p4 + pe) + d * x0 + x2 with
-      // row = x0 e1 + x1
-      const int x0 = l0[0] - mn[0], row = x0 * e1 + (l0[1] - mn[1]);
-      // a table per candidate and pass of kPass lanes, one slot per bank
-      // group (cell address mod kPass) plus one for invalid lanes
-      constexpr int kPass = 128 / (int)sizeof(T), kPasses = 64 / kPass;
-      int *tab = reinterpret_cast<int *>(brick) + (t / kPass) * (kPass + 1);
-      int addr[kLayouts], slot[kLayouts];
-      int a_pe = row * p4 + (l0[2] - mn[2]);
-#pragma unroll
-      for (int pe = 0; pe < 4; ++pe) {
-        int a = a_pe;
-#pragma unroll
-        for (int dd = 0; dd < 2; ++dd) {
-          const int c = 2 * pe + dd;
-          addr[c] = a;
-          slot[c] = kPasses * c * (kPass + 1) + (valid ? (a & (kPass - 1)) : kPass);
-          tab[slot[c]] = a;
-          a += 2 * x0;
-        }
-        a_pe += row;
-      }
-      // The read-back must see the other lanes' writes, not this lane's own
-      // store forwarded by the compiler: a compiler memory barrier keeps the
-      // loads after the stores, and a wavefront's LDS accesses complete in
-      // order, so every write has landed before the reads.
-      __asm__ __volatile__("" ::: "memory");
-      int got[kLayouts];
-#pragma unroll
-      for (int c = 0; c < kLayouts; ++c) got[c] = tab[slot[c]];
-      int best_key = 0x7fffffff;
-#pragma unroll
-      for (int c = 0; c < kLayouts; ++c) {
-        const int n = __popcll(__ballot(valid && got[c] != addr[c]));
-        best_key = min(best_key, (n << 4) | c);
-      }
-      if (t == 0) layout[0] = best_key & 15;   // c < 8
-    }
-  }
-  if (use_lds) __syncthreads();
-  int p2 = p4, s0 = e1 * p4;
-  if (choose) {
-    const int best = layout[0];
-    p2 = p4 + (best >> 1);
-    s0 = e1 * p2 + 2 * (best & 1);
-  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const T *u = static_cast<const T *>(u_);
-  if (use_lds) {
-    // The brick holds e0 x e1 rows of e2 cells.  When a row neither wraps
-    // nor reaches the end of a fine-grid row, it is moved in 16-byte
-    // segments (kVec cells; the last segment may read up to kVec - 1 cells
-    // past the brick row, still inside the same fine-grid row, into the
-    // row's padding); otherwise one cell at a time.  Several loads per
-    // thread are in flight before their stores.  Quotients by small extents
-    // e <= 64 use a float reciprocal: the exact quotient (n + 1/2) / e lies
-    // at least 1 / (2 e) >= 1/128 from an integer, far above the product's
-    // error (quotients below 2^13, the reciprocal within 1 ulp).
-    const int g2 = wrap[2][0];
-    const bool rows_contiguous = g2 + p4 <= nf;
-    const float inv_e1 = __builtin_amdgcn_rcpf((float)e1);
-    if (rows_contiguous) {
-      const int items = e0 * e1 * nseg;
-      const float inv_ns = __builtin_amdgcn_rcpf((float)nseg);
-      for (int c0 = threadIdx.x; c0 < items; c0 += 4 * kTile) {
-        T v[4][kVec];
-        int dst[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = c0 + k * kTile;
-          if (c < items) {
-            const int r = (int)(((float)c + 0.5f) * inv_ns);
-            const int q = c - r * nseg;
-            const int a = (int)(((float)r + 0.5f) * inv_e1);
-            const int b = r - a * e1;
-            const T *src = u + (wrap[0][a] + wrap[1][b] + g2 + q * kVec);
-            __builtin_memcpy(&v[k][0], src, 16);
-            dst[k] = a * s0 + b * p2 + q * kVec;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (c0 + k * kTile < items) {
-#pragma unroll
-            for (int e = 0; e < kVec; ++e) brick[dst[k] + e] = v[k][e];
-          }
-        }
-      }
-    } else {
-      const int cells = e0 * e1 * e2;
-      const float inv_e2 = __builtin_amdgcn_rcpf((float)e2);
-      for (int c0 = threadIdx.x; c0 < cells; c0 += 8 * kTile) {
-        T v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int c = c0 + k * kTile;
-          if (c < cells) {
-            const int r = (int)(((float)c + 0.5f) * inv_e2);
-            const int cc = c - r * e2;
-            const int a = (int)(((float)r + 0.5f) * inv_e1);
-            const int b = r - a * e1;
-            v[k] = u[wrap[0][a] + wrap[1][b] + wrap[2][cc]];
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int c = c0 + k * kTile;
-          if (c < cells) {
-            const int r = (int)(((float)c + 0.5f) * inv_e2);
-            const int a = (int)(((float)r + 0.5f) * inv_e1);
-            brick[a * s0 + (r - a * e1) * p2 + (c - r * e2)] = v[k];
-          }
-        }
-      }
-    }
-  }
-  float w0[W], w1[W], w2[W];
-  if (valid) {
-    es_weights<W>(frac[0], beta, w0);
-    es_weights<W>(frac[1], beta, w1);
-    es_weights<W>(frac[2], beta, w2);
-  }
-  if (use_lds) __syncthreads();
-  if (!inb) return;
-  const int64_t o = m * P + perm[i];
-  if (!valid) {
-    const float nan = __uint_as_float(0x7fc00000u);
-    if (CPLX) {
-      if (out_) static_cast<float2 *>(out_)[o] = make_float2(nan, nan);
-    } else {
-      if (out_) static_cast<float *>(out_)[o] = nan;
-    }
-    return;
-  }
   float sr = 0.f, si = 0.f;
-  if (use_lds) {
-    const int base = (l0[0] - mn[0]) * s0 + (l0[1] - mn[1]) * p2 + (l0[2] - mn[2]);
+  // One brick: that of wavefronts first .. first + gw - 1 (whole: all four),
+  // staged by the block and read by them.
+  auto pass = [&](auto whole_, const BrickBox<W, kVec> &bk, int first, int gw) {
+    constexpr bool whole = decltype(whole_)::value;
+    const bool mine = whole || (wave >= first && wave < first + gw);
+    const int e0 = bk.e[0], e1 = bk.e[1], e2 = bk.e[2];
+    // Brick layout: cell (x0, x1, x2) at x0 * s0 + x1 * p2 + x2, with the row
+    // pitch p2 >= p4 (e2 rounded up to whole 16-byte segments, so a segment
+    // store never spills into the next row) and the plane stride
+    // s0 >= e1 * p2.  The small paddings are chosen per block: a wavefront's
+    // 64 lanes read 64 cells at a common offset from their support origins,
+    // so the LDS bank conflicts of every gather read are those of the lanes'
+    // origin addresses.  The first wavefront scores each candidate layout by
+    // letting every lane write its origin address into a table slot named by
+    // the address's bank group (one table per LDS pass of lanes) and read the
+    // slot back: a lane that finds another address there shares its banks
+    // with a different cell in its pass.  The candidate with the fewest such
+    // lanes wins (ties: the first); the other wavefronts' patches lie next to
+    // the first's, under the same rotation, and share its choice.  Eight
+    // candidates (row paddings 0-3, plane offsets 0 and 2) choose as well as
+    // sixteen (offsets 0-3) at half the probe's cost.
+    const int nseg = (e2 + kVec - 1) / kVec;
+    const int p4 = nseg * kVec;
+    const bool use_lds = bk.any && (whole || bk.fits(kCap));
+    const bool choose = use_lds && e0 * (e1 * (p4 + 3) + 2) <= kCap;
+    if (!whole && use_lds) __syncthreads();   // the brick before is read
+    if (use_lds && wave == (whole ? 0 : first)) {
+      // fine-grid offsets of every brick plane, row and column, wrapped once
+      // per brick (n_f <= 1022, so n_f^3 cells index in 32 bits)
+      const int t = threadIdx.x & 63, half = nf >> 1;
+      if (t < e0) wrap[0][t] = wrap_mod(bk.mn[0] + t + half, nf) * nf * nf;
+      if (t < e1) wrap[1][t] = wrap_mod(bk.mn[1] + t + half, nf) * nf;
+      if (t < e2) wrap[2][t] = wrap_mod(bk.mn[2] + t + half, nf);
+      if (choose) {
+        // candidate c = 2 pe + d / 2: p2 = p4 + pe, s0 = e1 p2 + d (d = 0, 2),
+        // so the origin address is row * (p4 + pe) + d * x0 + x2 with
+        // row = x0 e1 + x1
+        const int x0 = l0[0] - bk.mn[0], row = x0 * e1 + (l0[1] - bk.mn[1]);
+        // a table per candidate and pass of kPass lanes, one slot per bank
+        // group (cell address mod kPass) plus one for invalid lanes
+        constexpr int kPass = 128 / (int)sizeof(T), kPasses = 64 / kPass;
+        int *tab = reinterpret_cast<int *>(brick) + (t / kPass) * (kPass + 1);
+        int addr[kLayouts], slot[kLayouts];
+        int a_pe = row * p4 + (l0[2] - bk.mn[2]);
 #pragma unroll
-    for (int a = 0; a < W; ++a) {
-      float pr = 0.f, pi = 0.f;
+        for (int pe = 0; pe < 4; ++pe) {
+          int a = a_pe;
 #pragma unroll
-      for (int b = 0; b < W; ++b) {
-        const T *row = brick + base + a * s0 + b * p2;
-        float rr = 0.f, ri = 0.f;
+          for (int dd = 0; dd < 2; ++dd) {
+            const int c = 2 * pe + dd;
+            addr[c] = a;
+            slot[c] = kPasses * c * (kPass + 1) + (valid ? (a & (kPass - 1)) : kPass);
+            tab[slot[c]] = a;
+            a += 2 * x0;
+          }
+          a_pe += row;
+        }
+        // The read-back must see the other lanes' writes, not this lane's own
+        // store forwarded by the compiler: a compiler memory barrier keeps the
+        // loads after the stores, and a wavefront's LDS accesses complete in
+        // order, so every write has landed before the reads.
+        __asm__ __volatile__("" ::: "memory");
+        int got[kLayouts];
 #pragma unroll
-        for (int c = 0; c < W; ++c) {
-          if constexpr (CPLX) {
-            const float2 v = row[c];
-            rr = fmaf(w2[c], v.x, rr);
-            ri = fmaf(w2[c], v.y, ri);
-          } else {
-            rr = fmaf(w2[c], row[c], rr);
+        for (int c = 0; c < kLayouts; ++c) got[c] = tab[slot[c]];
+        int best_key = 0x7fffffff;
+#pragma unroll
+        for (int c = 0; c < kLayouts; ++c) {
+          const int n = __popcll(__ballot(valid && got[c] != addr[c]));
+          best_key = min(best_key, (n << 4) | c);
+        }
+        if (t == 0) layout[0] = best_key & 15;   // c < 8
+      }
+    }
+    if (use_lds) __syncthreads();
+    int p2 = p4, s0 = e1 * p4;
+    if (choose) {
+      const int best = layout[0];
+      p2 = p4 + (best >> 1);
+      s0 = e1 * p2 + 2 * (best & 1);
+    }
+    if (use_lds) {
+      // The brick holds e0 x e1 rows of e2 cells.  When a row neither wraps
+      // nor reaches the end of a fine-grid row, it is moved in 16-byte
+      // segments (kVec cells; the last segment may read up to kVec - 1 cells
+      // past the brick row, still inside the same fine-grid row, into the
+      // row's padding); otherwise one cell at a time.  Several loads per
+      // thread are in flight before their stores.  Quotients by small extents
+      // e <= 64 use a float reciprocal: the exact quotient (n + 1/2) / e lies
+      // at least 1 / (2 e) >= 1/128 from an integer, far above the product's
+      // error (quotients below 2^13, the reciprocal within 1 ulp).
+      const int g2 = wrap[2][0];
+      const bool rows_contiguous = g2 + p4 <= nf;
+      const float inv_e1 = __builtin_amdgcn_rcpf((float)e1);
+      if (rows_contiguous) {
+        const int items = e0 * e1 * nseg;
+        const float inv_ns = __builtin_amdgcn_rcpf((float)nseg);
+        for (int c0 = threadIdx.x; c0 < items; c0 += 4 * kTile) {
+          T v[4][kVec];
+          int dst[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int c = c0 + k * kTile;
+            if (c < items) {
+              const int r = (int)(((float)c + 0.5f) * inv_ns);
+              const int q = c - r * nseg;
+              const int a = (int)(((float)r + 0.5f) * inv_e1);
+              const int b = r - a * e1;
+              const T *src = u + (wrap[0][a] + wrap[1][b] + g2 + q * kVec);
+              __builtin_memcpy(&v[k][0], src, 16);
+              dst[k] = a * s0 + b * p2 + q * kVec;
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (c0 + k * kTile < items) {
+#pragma unroll
+              for (int e = 0; e < kVec; ++e) brick[dst[k] + e] = v[k][e];
+            }
           }
         }
-        pr = fmaf(w1[b], rr, pr);
-        if (CPLX) pi = fmaf(w1[b], ri, pi);
-      }
-      sr = fmaf(w0[a], pr, sr);
-      if (CPLX) si = fmaf(w0[a], pi, si);
-    }
-  } else {
-    int g0[W], g1[W], g2[W];
+      } else {
+        const int cells = e0 * e1 * e2;
+        const float inv_e2 = __builtin_amdgcn_rcpf((float)e2);
+        for (int c0 = threadIdx.x; c0 < cells; c0 += 8 * kTile) {
+          T v[8];
 #pragma unroll
-    for (int a = 0; a < W; ++a) {
-      g0[a] = wrap_mod(l0[0] + a + (nf >> 1), nf);
-      g1[a] = wrap_mod(l0[1] + a + (nf >> 1), nf);
-      g2[a] = wrap_mod(l0[2] + a + (nf >> 1), nf);
-    }
+          for (int k = 0; k < 8; ++k) {
+            const int c = c0 + k * kTile;
+            if (c < cells) {
+              const int r = (int)(((float)c + 0.5f) * inv_e2);
+              const int cc = c - r * e2;
+              const int a = (int)(((float)r + 0.5f) * inv_e1);
+              const int b = r - a * e1;
+              v[k] = u[wrap[0][a] + wrap[1][b] + wrap[2][cc]];
+            }
+          }
 #pragma unroll
-    for (int a = 0; a < W; ++a) {
-      float pr = 0.f, pi = 0.f;
-#pragma unroll
-      for (int b = 0; b < W; ++b) {
-        const T *row = u + ((int64_t)g0[a] * nf + g1[b]) * nf;
-        float rr = 0.f, ri = 0.f;
-#pragma unroll
-        for (int c = 0; c < W; ++c) {
-          if constexpr (CPLX) {
-            const float2 v = row[g2[c]];
-            rr = fmaf(w2[c], v.x, rr);
-            ri = fmaf(w2[c], v.y, ri);
-          } else {
-            rr = fmaf(w2[c], row[g2[c]], rr);
+          for (int k = 0; k < 8; ++k) {
+            const int c = c0 + k * kTile;
+            if (c < cells) {
+              const int r = (int)(((float)c + 0.5f) * inv_e2);
+              const int a = (int)(((float)r + 0.5f) * inv_e1);
+              brick[a * s0 + (r - a * e1) * p2 + (c - r * e2)] = v[k];
+            }
           }
         }
-        pr = fmaf(w1[b], rr, pr);
-        if (CPLX) pi = fmaf(w1[b], ri, pi);
       }
-      sr = fmaf(w0[a], pr, sr);
-      if (CPLX) si = fmaf(w0[a], pi, si);
+    }
+    float w0[W], w1[W], w2[W];
+    if (mine && valid) {
+      es_weights<W>(frac[0], beta, w0);
+      es_weights<W>(frac[1], beta, w1);
+      es_weights<W>(frac[2], beta, w2);
+    }
+    if (use_lds) __syncthreads();
+    if (!(mine && valid)) return;
+    if (use_lds) {
+      const int base = (l0[0] - bk.mn[0]) * s0 + (l0[1] - bk.mn[1]) * p2 + (l0[2] - bk.mn[2]);
+#pragma unroll
+      for (int a = 0; a < W; ++a) {
+        float pr = 0.f, pi = 0.f;
+#pragma unroll
+        for (int b = 0; b < W; ++b) {
+          const T *row = brick + base + a * s0 + b * p2;
+          float rr = 0.f, ri = 0.f;
+#pragma unroll
+          for (int c = 0; c < W; ++c) {
+            if constexpr (CPLX) {
+              const float2 v = row[c];
+              rr = fmaf(w2[c], v.x, rr);
+              ri = fmaf(w2[c], v.y, ri);
+            } else {
+              rr = fmaf(w2[c], row[c], rr);
+            }
+          }
+          pr = fmaf(w1[b], rr, pr);
+          if (CPLX) pi = fmaf(w1[b], ri, pi);
+        }
+        sr = fmaf(w0[a], pr, sr);
+        if (CPLX) si = fmaf(w0[a], pi, si);
+      }
+    } else if constexpr (!whole) {
+      int base[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) base[d] = wrap_mod(l0[d] + (nf >> 1), nf);
+      gather_support<W, CPLX>(u, nf, base, w0, w1, w2, sr, si);
+    }
+  };
+  // The whole tile shares a brick where that fits (16 x 16 points up to about
+  // 0.8 cells apart); otherwise two pairs of wavefronts, or each wavefront by
+  // itself, in turn (their points are runs of the Hilbert order, hence smaller
+  // patches), and a wavefront whose own brick does not fit reads the grid.  Per
+  // point of a REAL 130^3 grid: 0.033 ns by tiles (128^2 pixels), 0.242 at 96^2
+  // pixels and 0.470 at 64^2 when a tile that did not fit read the grid, 0.048
+  // and 0.065 by parts of it.
+  const BrickBox<W, kVec> all = brick_of<W, kVec>(red, 0, 4);
+  if (all.fits(kCap)) {
+    pass(std::true_type{}, all, 0, 4);
+  } else {
+    const int gw = brick_of<W, kVec>(red, 0, 2).fits(kCap) && brick_of<W, kVec>(red, 2, 2).fits(kCap) ? 2 : 1;
+#pragma unroll 1
+    for (int first = 0; first < 4; first += gw) {
+      // (kept inside the loop: hoisted, the weights' registers would be held
+      // while the bricks are staged)
+      __asm__ __volatile__("" : "+v"(frac[0]), "+v"(frac[1]), "+v"(frac[2]), "+v"(l0[0]), "+v"(l0[1]), "+v"(l0[2]));
+      pass(std::false_type{}, brick_of<W, kVec>(red, first, gw), first, gw);
     }
   }
-  if (CPLX) {
-    if (out_) static_cast<float2 *>(out_)[o] = make_float2(sr, si);
-  } else {
-    if (out_) static_cast<float *>(out_)[o] = sr;
-  }
+  if (!inb || !out_) return;
+  if (!valid) sr = si = __uint_as_float(0x7fc00000u);
+  const int64_t o = m * P + perm[i];
+  if constexpr (CPLX)
+    static_cast<float2 *>(out_)[o] = make_float2(sr, si);
+  else
+    static_cast<float *>(out_)[o] = sr;
 }
 
 template <int W>
