@@ -53,23 +53,19 @@ __device__ inline void tile_of_block(int tiles_m, int tiles_n, int splits, int &
 constexpr int kBK = 32;         // floats of P per K step
 constexpr int kLdF = kBK + 4;   // LDS row stride (floats)
 
-// Four consecutive values X[r][k..k+3] of a row of length ld, zero beyond
-// row `rows` or column `kend` (kend <= ld).  Whole quads take one load at
-// whatever alignment the row has (odd row lengths, such as a detector behind
-// a beam stop, leave rows on 4-byte boundaries; loading their values one by
-// one took 2.3 times as long on 512 x 256 x 4,095).
-__device__ inline float4 load_row4(const float *__restrict__ X, int64_t rows, int64_t r,
-                                   int64_t kend, int64_t k, int64_t ld) {
+// Four consecutive values p[0..3] of a row, zero from the n-th on (n may be
+// negative).  Whole quads take one load at whatever alignment the row has (odd
+// row lengths, such as a detector behind a beam stop: four single loads
+// instead of one took 2.3 times as long on 512 x 256 x 4,095).
+__device__ inline float4 load_quad(const float *__restrict__ p, int n) {
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (r >= rows) return v;
-  const float *p = X + r * ld + k;
-  if (k + 4 <= kend) {
+  if (n >= 4) {
     __builtin_memcpy(&v, p, 16);
     return v;
   }
-  v.x = k < kend ? p[0] : 0.f;
-  v.y = k + 1 < kend ? p[1] : 0.f;
-  v.z = k + 2 < kend ? p[2] : 0.f;
+  v.x = n > 0 ? p[0] : 0.f;
+  v.y = n > 1 ? p[1] : 0.f;
+  v.z = n > 2 ? p[2] : 0.f;
   return v;
 }
 
@@ -77,67 +73,75 @@ __device__ inline float4 load_row4(const float *__restrict__ X, int64_t rows, in
 // kchunk) and stores its partial tile, row-major; reduce_f32_kernel adds the
 // partials in split order and runs the epilogue.
 //
-// 512 threads = 8 wavefronts as 2 (M) x 4 (N); each wavefront owns a 64 x 32
-// quarter-column of the 128 x 128 tile (two 32x32 MFMA accumulators plus two
-// per-K-step partials), which keeps the register count low enough for four
-// wavefronts per SIMD.
-constexpr int kF32Threads = 512;
-
-__global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) void match_f32_kernel(
+// Tiles of T x T outputs by 4 T threads, wavefronts as 2 (M) x T / 32 (N).
+// T = 128: each wavefront owns a 64 x 32 quarter-column (two 32x32 MFMA
+// accumulators plus two per-K-step partials), which keeps the register count
+// low enough for four wavefronts per SIMD.  T = 64, for launches that would
+// leave CUs idle: one 32 x 32 accumulator a wavefront, and with few
+// wavefronts to hide them the loads run four K steps ahead.  The sums of an
+// output run over K in the same order either way.
+template <int T>
+__global__ __launch_bounds__(4 * T) __attribute__((amdgpu_waves_per_eu(T == 128 ? 4 : 1, 4))) void match_f32_kernel(
     const float *__restrict__ S, const float *__restrict__ D, const float *__restrict__ sn,
     const float *__restrict__ dn, int64_t M, int64_t N, int64_t P, uint32_t m_offset,
     unsigned long long *__restrict__ keys, int tiles_m, int tiles_n, int splits, int64_t kchunk,
     float *__restrict__ partials) {
+  constexpr int kThreads = 4 * T, kI = T / 64, kAhead = T == 128 ? 1 : 4;
   // double-buffered A/B stages: one barrier per K step
-  __shared__ __attribute__((aligned(16))) float As[2][kBM * kLdF];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kBN * kLdF];
-  __shared__ float sns[kBM], dns[kBN];
-  __shared__ unsigned long long red[2][kBN];
+  __shared__ __attribute__((aligned(16))) float As[2][T * kLdF];
+  __shared__ __attribute__((aligned(16))) float Bs[2][T * kLdF];
+  __shared__ float sns[T], dns[T];
+  __shared__ unsigned long long red[2][T];
 
   int tm, tn, split;
   tile_of_block(tiles_m, tiles_n, splits, tm, tn, split);
-  const int64_t row0 = (int64_t)tm * kBM, col0 = (int64_t)tn * kBN;
+  const int64_t row0 = (int64_t)tm * T, col0 = (int64_t)tn * T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3, lr = lane & 31, lh = lane >> 5;
+  const int wm = wave / (T / 32), wn = wave % (T / 32), lr = lane & 31, lh = lane >> 5;
   const int64_t kbeg = (int64_t)split * kchunk;
   const int64_t kend = min(P, kbeg + kchunk);
 
-  float4 ra[2], rb[2];
-  auto gload = [&](int64_t k0) {
+  // Rows past the last read the last one (their outputs are not used), so that
+  // whole K steps load without a branch: with one, each step waited for its
+  // own loads.
+  float4 ra[kAhead][2], rb[kAhead][2];
+  const float *pa[2], *pb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int id = tid + kThreads * i, r = id >> 3, c = (id & 7) * 4;
+    pa[i] = S + min(row0 + r, M - 1) * P + c;
+    pb[i] = D + min(col0 + r, N - 1) * P + c;
+  }
+  const int whole = kend > kbeg ? (int)((kend - kbeg) / kBK) : 0;   // whole K steps
+  auto gload = [&](int step, int set) {   // steps past the last whole one load that
+    const int64_t k = kbeg + (int64_t)min(step, whole - 1) * kBK;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int id = tid + kF32Threads * i, r = id >> 3, c = (id & 7) * 4;
-      ra[i] = load_row4(S, M, row0 + r, kend, k0 + c, P);
-      rb[i] = load_row4(D, N, col0 + r, kend, k0 + c, P);
+      __builtin_memcpy(&ra[set][i], pa[i] + k, 16);
+      __builtin_memcpy(&rb[set][i], pb[i] + k, 16);
     }
   };
 
-  floatx16 acc[2];
+  floatx16 acc[kI];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < kI; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 
-  auto lstore = [&](int buf) {
+  auto lstore = [&](int buf, int set) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int id = tid + kF32Threads * i, r = id >> 3, c = (id & 7) * 4;
-      *reinterpret_cast<float4 *>(&As[buf][r * kLdF + c]) = ra[i];
-      *reinterpret_cast<float4 *>(&Bs[buf][r * kLdF + c]) = rb[i];
+      const int id = tid + kThreads * i, r = id >> 3, c = (id & 7) * 4;
+      *reinterpret_cast<float4 *>(&As[buf][r * kLdF + c]) = ra[set][i];
+      *reinterpret_cast<float4 *>(&Bs[buf][r * kLdF + c]) = rb[set][i];
     }
   };
-  gload(kbeg);
-  lstore(0);
-  __syncthreads();
-  int buf = 0;
-  for (int64_t k0 = kbeg; k0 < kend; k0 += kBK) {
-    const bool more = k0 + kBK < kend;
-    if (more) gload(k0 + kBK);
+  auto multiply = [&](int buf) {
     // Fresh partial sums per K step keep every accumulation chain short:
     // at most 2 kBK roundings inside the step plus one per step.
-    floatx16 part[2];
+    floatx16 part[kI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) part[i][r] = 0.f;
     const float *A = As[buf], *B = Bs[buf];
@@ -146,40 +150,73 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int kk = 0; kk < kBK / 8; ++kk) {
-      float4 a[2];
+      float4 a[kI];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const float4 *>(&A[(wm * 64 + i * 32 + lr) * kLdF + kk * 8 + lh * 4]);
+      for (int i = 0; i < kI; ++i)
+        a[i] = *reinterpret_cast<const float4 *>(&A[(wm * 32 * kI + i * 32 + lr) * kLdF + kk * 8 + lh * 4]);
       const float4 b = *reinterpret_cast<const float4 *>(&B[(wn * 32 + lr) * kLdF + kk * 8 + lh * 4]);
       // Lane half lh supplies k = 4 lh + e for MFMA e: A and B use the same
       // permutation of the 8 k values, so the sum is unchanged.
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < kI; ++i)
           part[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[e], part[i], 0, 0, 0);
     }
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) acc[i] += part[i];
-    if (more) lstore(buf ^ 1);
+    for (int i = 0; i < kI; ++i) acc[i] += part[i];
+  };
+  // step s: loads of step s + kAhead into the set that step s was stored from,
+  // products from stage s % 2, step s + 1 stored to the other
+  auto step = [&](int s, int u) {
+    gload(s + kAhead, u % kAhead);
+    multiply(u & 1);
+    lstore((u + 1) & 1, (u + 1) % kAhead);
     __syncthreads();
-    buf ^= 1;
+  };
+  constexpr int kU = kAhead > 2 ? kAhead : 2;
+  if (whole > 0) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) gload(d, d);
+    lstore(0, 0);
+    __syncthreads();
+    int s = 0;
+    for (; s + kU <= whole; s += kU) {
+#pragma unroll
+      for (int u = 0; u < kU; ++u) step(s + u, u);
+    }
+#pragma unroll
+    for (int u = 0; u < kU - 1; ++u)
+      if (s + u < whole) step(s + u, u);
+  }
+  const int64_t k0 = kbeg + (int64_t)whole * kBK;
+  if (k0 < kend) {   // the ragged step
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = ((tid + kThreads * i) & 7) * 4;
+      ra[0][i] = load_quad(pa[i] + k0, (int)(kend - k0) - c);
+      rb[0][i] = load_quad(pb[i] + k0, (int)(kend - k0) - c);
+    }
+    lstore(whole & 1, 0);
+    __syncthreads();
+    multiply(whole & 1);
+    __syncthreads();
   }
 
   if (splits > 1) {
-    float *mine = partials + ((int64_t)(tm * tiles_n + tn) * splits + split) * (kBM * kBN);
+    float *mine = partials + ((int64_t)(tm * tiles_n + tn) * splits + split) * (T * T);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        mine[(wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * kBN + wn * 32 + lr] = acc[i][r];
+        mine[(wm * 32 * kI + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * T + wn * 32 + lr] = acc[i][r];
     return;
   }
-  if (tid < kBM) {
+  if (tid < T) {
     sns[tid] = row0 + tid < M ? sn[row0 + tid] : 0.f;
-  } else if (tid < kBM + kBN) {
-    const int c = tid - kBM;
+  } else if (tid < 2 * T) {
+    const int c = tid - T;
     dns[c] = col0 + c < N ? dn[col0 + c] : 0.f;
   }
   __syncthreads();
@@ -187,12 +224,12 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
     const int cl = wn * 32 + lr;
     unsigned long long best = ~0ull;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         // 32x32 MFMA output layout: lane holds column lane % 32 and rows
         // 8 (r / 4) + 4 (lane / 32) + r % 4.
-        const int rl = wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
+        const int rl = wm * 32 * kI + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
         if (row0 + rl < M) {
           const float d = fmaf(-2.0f, acc[i][r], sns[rl] + dns[cl]);
           const unsigned long long key =
@@ -205,7 +242,7 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
     if (lh == 0) red[wm][cl] = best;
   }
   __syncthreads();
-  if (tid < kBN) {
+  if (tid < T) {
     const unsigned long long a = red[0][tid], b = red[1][tid];
     const unsigned long long k = a < b ? a : b;
     if (col0 + tid < N && k != ~0ull) atomicMin(keys + col0 + tid, k);
@@ -213,35 +250,38 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4, 
 }
 
 // Sum of element (row, col) of a tile's partials in split order.
+template <int T = kBM>
 __device__ inline float split_sum(const float *__restrict__ part, int splits, int row, int col) {
-  const float *p = part + row * kBN + col;
+  const float *p = part + row * T + col;
   float v = 0.f;
 #pragma unroll 4
-  for (int sp = 0; sp < splits; ++sp) v += p[(int64_t)sp * (kBM * kBN)];
+  for (int sp = 0; sp < splits; ++sp) v += p[(int64_t)sp * (T * T)];
   return v;
 }
 
 // Epilogue of a split launch: a block takes 32 columns of a tile, a thread 16
-// rows of one of them.
+// (tiles of 64: 8) rows of one of them.
 constexpr int kRedCols = 32, kRedRows = kBM / (256 / kRedCols);
 
+template <int T>
 __global__ __launch_bounds__(256) void reduce_f32_kernel(
     const float *__restrict__ partials, int splits, const float *__restrict__ sn,
     const float *__restrict__ dn, int64_t M, int64_t N, uint32_t m_offset, int tiles_n,
     unsigned long long *__restrict__ keys) {
+  constexpr int kRows = T / (256 / kRedCols);
   __shared__ unsigned long long red[256];
-  const int tile = blockIdx.x / (kBN / kRedCols), c0 = (blockIdx.x % (kBN / kRedCols)) * kRedCols;
+  const int tile = blockIdx.x / (T / kRedCols), c0 = (blockIdx.x % (T / kRedCols)) * kRedCols;
   const int col = c0 + (threadIdx.x & (kRedCols - 1)), rg = threadIdx.x / kRedCols;
-  const int64_t row0 = (int64_t)(tile / tiles_n) * kBM, n = (int64_t)(tile % tiles_n) * kBN + col;
-  const float *part = partials + (int64_t)tile * splits * (kBM * kBN);
+  const int64_t row0 = (int64_t)(tile / tiles_n) * T, n = (int64_t)(tile % tiles_n) * T + col;
+  const float *part = partials + (int64_t)tile * splits * (T * T);
   unsigned long long best = ~0ull;
   if (n < N) {
     const float dnn = dn[n];
 #pragma unroll 4
-    for (int j = 0; j < kRedRows; ++j) {
-      const int row = rg * kRedRows + j;
+    for (int j = 0; j < kRows; ++j) {
+      const int row = rg * kRows + j;
       if (row0 + row >= M) break;
-      const float d = fmaf(-2.0f, split_sum(part, splits, row, col), sn[row0 + row] + dnn);
+      const float d = fmaf(-2.0f, split_sum<T>(part, splits, row, col), sn[row0 + row] + dnn);
       const unsigned long long key =
           ((unsigned long long)float_key(d) << 32) | (uint32_t)(m_offset + (uint32_t)(row0 + row));
       best = key < best ? key : best;
@@ -295,48 +335,88 @@ static bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) =
 // chip (256 CUs x 2).
 constexpr int kSlots = 512;
 
-// K splits of a launch of 128 x 128 tiles: enough to give every resident
-// block a share, each at least 512 values of P long (16 FP32 or 8 BF16 K
-// steps).  Only launches of under half a round of tiles are split: blocks are
+static int64_t tiles_of(int64_t M, int64_t N, int T) { return ((M + T - 1) / T) * ((N + T - 1) / T); }
+
+// K splits of an FP32 launch: the count up to four that best fills the chip's
+// resident blocks with 128 x 128 tiles, each split at least 1024 values of P
+// long.  Only launches of under half a round of tiles are split: blocks are
 // dispatched dynamically, so a partial last round costs less than the
 // partial tiles' extra traffic (measured on 1,264 tiles of K = 16,384:
-// unsplit 5.8 ms, two splits 6.7 ms).
-static int tile_splits(int64_t M, int64_t N, int64_t P) {
-  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  if (tiles == 0 || 2 * tiles >= kSlots) return 1;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(kSlots / tiles, P / 512));
+// unsplit 5.8 ms, two splits 6.7 ms).  The distances are differences of
+// nearly equal sums, so their rounding shows the order of those: more splits,
+// down to 512 values, moved distances of Poisson images by up to 3e-5 of
+// themselves.
+static int f32_splits(int64_t M, int64_t N, int64_t P) {
+  const int64_t tiles = tiles_of(M, N, kBM);
+  if (2 * tiles >= kSlots) return 1;
+  int best = 1;
+  double best_eff = 0.0;
+  for (int s = 1; s <= 4; ++s) {
+    if (s > 1 && P / s < 1024) break;
+    const int64_t units = tiles * s;
+    const int64_t rounds = (units + kSlots - 1) / kSlots;
+    const double eff = (double)units / (double)(rounds * kSlots);
+    if (eff > best_eff + 0.02) {
+      best_eff = eff;
+      best = s;
+    }
+  }
+  return best;
 }
 
-static size_t partial_bytes(int64_t M, int64_t N, int64_t P) {
-  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  const int s = tile_splits(M, N, P);
-  return s > 1 ? (size_t)tiles * s * kBM * kBN * sizeof(float) : 0;
+// Blocks of 128 x 128 outputs for fewer than three quarters of the CUs: tiles
+// of a quarter, four times as many blocks of half the matrix instructions per
+// K step and wavefront.  Whole calls, 128- and 64-tiles: one block of 128
+// (128 x 64 x 4,096) 278 and 100 us; 64 (1,000 x 256 x 4,096) 91 and 44; 128
+// (1,000 x 512 x 4,096) 92 and 62; 240 (1,920 x 512 x 4,096) 97 and 102; 480
+// (2,560 x 768 x 4,096) 167 and 175.
+static bool f32_small(int64_t M, int64_t N, int64_t P) {
+  return tiles_of(M, N, kBM) * f32_splits(M, N, P) < kSlots * 3 / 8;
 }
 
 size_t match_f32_workspace_bytes(int64_t M, int64_t N, int64_t P) {
-  return (((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255) + partial_bytes(M, N, P);
+  const size_t keys = ((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255;
+  const int s = f32_splits(M, N, P), T = f32_small(M, N, P) ? 64 : kBM;
+  return keys + (s > 1 ? (size_t)tiles_of(M, N, T) * s * T * T * sizeof(float) : 0);
+}
+
+template <int T>
+static hipError_t match_f32_go(const float *S, const float *D, const float *sn, const float *dn,
+                               int64_t M, int64_t N, int64_t P, int64_t m_offset, int splits,
+                               unsigned long long *keys, float *partials, hipStream_t s) {
+  const int tiles_m = (int)((M + T - 1) / T), tiles_n = (int)((N + T - 1) / T);
+  const int64_t tiles = (int64_t)tiles_m * tiles_n, blocks = tiles * splits;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  // K chunk: a multiple of the K step
+  int64_t kchunk = (P + splits - 1) / splits;
+  kchunk = (kchunk + kBK - 1) / kBK * kBK;
+  hipLaunchKernelGGL((match_f32_kernel<T>), dim3((unsigned)blocks), dim3(4 * T), 0, s, S, D, sn, dn, M, N,
+                     P, (uint32_t)m_offset, keys, tiles_m, tiles_n, splits, kchunk, partials);
+  if (splits > 1)
+    hipLaunchKernelGGL((reduce_f32_kernel<T>), dim3((unsigned)(tiles * (T / kRedCols))), dim3(256), 0, s,
+                       partials, splits, sn, dn, M, N, (uint32_t)m_offset, tiles_n, keys);
+  return hipGetLastError();
 }
 
 hipError_t launch_match_f32(const float *S, const float *D, const float *sn, const float *dn,
                             int64_t M, int64_t N, int64_t P, int64_t m_offset, void *workspace,
                             hipStream_t s) {
-  const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-  const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  const int splits = tile_splits(M, N, P);
-  const int64_t blocks = tiles * splits;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  // K chunk: a multiple of the K step
-  int64_t kchunk = (P + splits - 1) / splits;
-  kchunk = (kchunk + kBK - 1) / kBK * kBK;
   char *ws = static_cast<char *>(workspace);
   auto *keys = reinterpret_cast<unsigned long long *>(ws);
   float *partials = reinterpret_cast<float *>(ws + (((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255));
-  hipLaunchKernelGGL(match_f32_kernel, dim3((unsigned)blocks), dim3(kF32Threads), 0, s, S, D, sn, dn, M, N,
-                     P, (uint32_t)m_offset, keys, tiles_m, tiles_n, splits, kchunk, partials);
-  if (splits > 1)
-    hipLaunchKernelGGL(reduce_f32_kernel, dim3((unsigned)(tiles * (kBN / kRedCols))), dim3(256), 0, s,
-                       partials, splits, sn, dn, M, N, (uint32_t)m_offset, tiles_n, keys);
-  return hipGetLastError();
+  const int splits = f32_splits(M, N, P);
+  return f32_small(M, N, P) ? match_f32_go<64>(S, D, sn, dn, M, N, P, m_offset, splits, keys, partials, s)
+                            : match_f32_go<kBM>(S, D, sn, dn, M, N, P, m_offset, splits, keys, partials, s);
+}
+
+// K splits of a BF16 launch of 128 x 128 tiles: enough to give every resident
+// block a share, each at least 512 values of P (8 K steps) long, under half a
+// round of tiles (the matrix products only choose the candidates whose exact
+// distances are formed, so their order of sums is free within its bound).
+static int bf16_splits(int64_t M, int64_t N, int64_t P) {
+  const int64_t tiles = tiles_of(M, N, kBM);
+  if (tiles == 0 || 2 * tiles >= kSlots) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kSlots / tiles, P / 512));
 }
 
 // ---------------------------------------------------------------- BF16 ----
@@ -751,7 +831,10 @@ __global__ __launch_bounds__(512, 1) void match_bf16_big_kernel(
   }
 }
 
-size_t match_bf16_partial_bytes(int64_t M, int64_t N, int64_t P) { return partial_bytes(M, N, P); }
+size_t match_bf16_partial_bytes(int64_t M, int64_t N, int64_t P) {
+  const int s = bf16_splits(M, N, P);
+  return s > 1 ? (size_t)tiles_of(M, N, kBM) * s * kBM * kBN * sizeof(float) : 0;
+}
 
 hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *sn,
                              const float *dn, int64_t M, int64_t N, int64_t P, uint32_t *cand,
@@ -765,7 +848,7 @@ hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *
     return hipGetLastError();
   }
   const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-  const int splits = tile_splits(M, N, P);
+  const int splits = bf16_splits(M, N, P);
   const int64_t tiles = (int64_t)tiles_m * tiles_n, blocks = tiles * splits;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const int64_t kchunk = ((P + splits - 1) / splits + kBKH - 1) / kBKH * kBKH;

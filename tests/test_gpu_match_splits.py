@@ -53,3 +53,22 @@ def test_split_and_ragged_launches(mode, M, N, P):
     assert np.array_equal(bi[decided], am[decided])
     am = bi
     assert np.all(np.abs(bd - ex[am, cols]) <= E[am, cols])
+
+
+@pytest.mark.parametrize("P", [31, 96, 700, 736])
+def test_fp32_distances_do_not_depend_on_the_tile_size(P):
+    """A launch of 2,100 x 2,050 runs in tiles of 128, its first 100 rows and 50
+    images alone in tiles of 64: the same sums in the same order, so the same
+    distances bit for bit (P with and without a ragged K step, and shorter than
+    the four steps that the small tiles load ahead)."""
+    g = np.random.default_rng(P)
+    S = g.gamma(2.0, 15.0, (2100, P)).astype(np.float32)
+    D = g.poisson(S[g.integers(0, 100, 2050)]).astype(np.float32)
+    got = []
+    for s, d in ((gpu(S), gpu(D)), (gpu(S[:100]), gpu(D[:50]))):
+        best = spfel.new_best(len(d), DEV)
+        spfel.match(s, spfel.row_norm2(s), d, spfel.row_norm2(d), *best)
+        got.append([host(b) for b in best])
+    same = got[0][0][:50] == got[1][0]   # a row past the first 100 may be nearer at short P
+    assert same.mean() >= (0.9 if P >= 96 else 0.1)
+    np.testing.assert_array_equal(got[0][1][:50][same], got[1][1][same])
