@@ -619,8 +619,7 @@ size_t spfel_match_workspace_bytes(int64_t M, int64_t n_img, int64_t P, int mode
   if (M < 0 || n_img < 0 || P < 0) return 0;
   size_t b = match_f32_workspace_bytes(M, n_img, P);
   if (mode == SPFEL_MATCH_BF16_RESCORE8)
-    b = align256(match_bf16_candidate_bytes(M, n_img)) + align256(match_rescore_bytes(n_img)) +
-        match_bf16_partial_bytes(M, n_img, P);
+    b = align256(match_bf16_candidate_bytes(M, n_img)) + match_rescore_bytes(n_img);
   return b < 256 ? 256 : b;
 }
 
@@ -665,8 +664,7 @@ int spfel_match(const void *slices, const float *slice_norm2,
     auto *cand = static_cast<uint32_t *>(workspace);
     char *scratch = static_cast<char *>(workspace) + align256(match_bf16_candidate_bytes(M, n_img));
     e = launch_match_bf16(static_cast<const uint16_t *>(slices), static_cast<const uint16_t *>(images),
-                          slice_norm2, image_norm2, M, n_img, P, cand,
-                          reinterpret_cast<float *>(scratch + align256(match_rescore_bytes(n_img))), s);
+                          slice_norm2, image_norm2, M, n_img, P, cand, s);
     if (e == hipSuccess)
       e = launch_rescore(cand, match_bf16_tile_rows(M, n_img, P, slices, images), M, n_img, P,
                          m_offset, slices_f32, images_f32, slice_norm2, image_norm2, slice_err,

@@ -147,12 +147,9 @@ hipError_t launch_match_f32(const float *S, const float *D, const float *sn,
 // 128-row tiling.
 int match_bf16_tile_rows(int64_t M, int64_t N, int64_t P, const void *S, const void *D);
 size_t match_bf16_candidate_bytes(int64_t M, int64_t N);
-// Partial tiles of a launch that splits K (0 bytes for others).
-size_t match_bf16_partial_bytes(int64_t M, int64_t N, int64_t P);
 hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D,
                              const float *sn, const float *dn, int64_t M,
-                             int64_t N, int64_t P, uint32_t *cand, float *partials,
-                             hipStream_t s);
+                             int64_t N, int64_t P, uint32_t *cand, hipStream_t s);
 // Certified rescore and fallback of the BF16 matcher.  scratch:
 // match_rescore_bytes(N) bytes, 256-byte aligned (chunk maxima, fallback
 // count, list and keys).

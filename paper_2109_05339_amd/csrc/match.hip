@@ -374,10 +374,18 @@ static bool f32_small(int64_t M, int64_t N, int64_t P) {
   return tiles_of(M, N, kBM) * f32_splits(M, N, P) < kSlots * 3 / 8;
 }
 
-size_t match_f32_workspace_bytes(int64_t M, int64_t N, int64_t P) {
+// Packed keys first.  A launch that splits K has its partial tiles at the
+// offset below: callers size their workspaces by this rule, with a reserved
+// word per 128 x 128 tile between the two (tiles of 64 never need more).
+static size_t f32_partials_at(int64_t M, int64_t N) {
   const size_t keys = ((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255;
-  const int s = f32_splits(M, N, P), T = f32_small(M, N, P) ? 64 : kBM;
-  return keys + (s > 1 ? (size_t)tiles_of(M, N, T) * s * T * T * sizeof(float) : 0);
+  return keys + (((size_t)tiles_of(M, N, kBM) * sizeof(unsigned) + 255) & ~(size_t)255);
+}
+
+size_t match_f32_workspace_bytes(int64_t M, int64_t N, int64_t P) {
+  const int s = f32_splits(M, N, P);
+  if (s == 1) return ((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255;
+  return f32_partials_at(M, N) + (size_t)tiles_of(M, N, kBM) * s * kBM * kBN * sizeof(float);
 }
 
 template <int T>
@@ -403,40 +411,27 @@ hipError_t launch_match_f32(const float *S, const float *D, const float *sn, con
                             hipStream_t s) {
   char *ws = static_cast<char *>(workspace);
   auto *keys = reinterpret_cast<unsigned long long *>(ws);
-  float *partials = reinterpret_cast<float *>(ws + (((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255));
+  float *partials = reinterpret_cast<float *>(ws + f32_partials_at(M, N));
   const int splits = f32_splits(M, N, P);
   return f32_small(M, N, P) ? match_f32_go<64>(S, D, sn, dn, M, N, P, m_offset, splits, keys, partials, s)
                             : match_f32_go<kBM>(S, D, sn, dn, M, N, P, m_offset, splits, keys, partials, s);
-}
-
-// K splits of a BF16 launch of 128 x 128 tiles: enough to give every resident
-// block a share, each at least 512 values of P (8 K steps) long, under half a
-// round of tiles (the matrix products only choose the candidates whose exact
-// distances are formed, so their order of sums is free within its bound).
-static int bf16_splits(int64_t M, int64_t N, int64_t P) {
-  const int64_t tiles = tiles_of(M, N, kBM);
-  if (tiles == 0 || 2 * tiles >= kSlots) return 1;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(kSlots / tiles, P / 512));
 }
 
 // ---------------------------------------------------------------- BF16 ----
 constexpr int kBKH = 64;          // bf16 values of P per K step
 constexpr int kLdH = kBKH + 8;    // LDS row stride (bf16 values)
 
-// Eight consecutive values of a row of length ld, zero beyond row `rows` or
-// column `kend`; whole groups in one load at whatever alignment the row has.
-__device__ inline uint4 load_row8h(const uint16_t *__restrict__ X, int64_t rows, int64_t r,
-                                   int64_t kend, int64_t k, int64_t ld) {
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (r >= rows) return v;
-  const uint16_t *p = X + r * ld + k;
-  if (k + 8 <= kend) {
+// Eight consecutive values p[0..7] of a row, zero from the n-th on (n may be
+// negative); whole groups in one load at whatever alignment the row has.
+__device__ inline uint4 load_oct(const uint16_t *__restrict__ p, int n) {
+  uint4 v;
+  if (n >= 8) {
     __builtin_memcpy(&v, p, 16);
     return v;
   }
   uint32_t h[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = k + e < kend ? p[e] : 0u;
+  for (int e = 0; e < 8; ++e) h[e] = e < n ? p[e] : 0u;
   return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
@@ -459,15 +454,17 @@ __device__ inline void insert8(unsigned long long (&top)[8], unsigned long long 
 }
 
 // The large-tile kernel is used when its 256 x 256 tiles occupy more than
-// half of the chip's 256 resident blocks, P is a whole number of its 64-wide K
-// steps and both operands are 16-byte aligned; otherwise 128 x 128 tiles.
-// Measured, large tiles against 128 x 128: 128 tiles 154 / 140 us (P = 4,096)
-// and 1,698 / 1,635 us (P = 65,536), 144 tiles 493 / 573 us, 288 tiles
-// 935 / 1,016 us, 320 tiles 1,188 / 1,314 us, 512 tiles 1,121 / 1,561 us.
+// half of the chip's 256 resident blocks, and where a second round of them is
+// at least a third full, P is a whole number of its 64-wide K steps and both
+// operands are 16-byte aligned; otherwise 128 x 128 tiles.  Measured (whole
+// calls), large tiles against 128 x 128: 132 tiles 176 / 175 us (P = 4,096);
+// 144 tiles 173 / 172 us (P = 4,096) and 541 / 566 us (16,384); 256 tiles 182 /
+// 216 us (4,096); at P = 16,384 288 tiles 1,006 / 928 us, 320 tiles 1,010 / 957
+// us, 512 tiles 1,149 / 1,488 us.
 int match_bf16_tile_rows(int64_t M, int64_t N, int64_t P, const void *S, const void *D) {
   if (P % 64 != 0 || !al16(S) || !al16(D)) return 128;
   const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-  return big > 136 ? 256 : 128;
+  return big > 136 && (big <= 256 || big > 336) ? 256 : 128;
 }
 
 // Candidate buffer for the 128-row tiling, the larger of the two.
@@ -479,100 +476,129 @@ size_t match_bf16_candidate_bytes(int64_t M, int64_t N) {
 // Candidate word: proxy-distance key with its 7 low bits replaced by the
 // row within the tile (a relative perturbation below 2^-15 of the proxy;
 // clearing or setting those bits bounds the proxy from below or above).
+//
+// Tiles of 128 rows by BN images, four wavefronts: 2 x 2 of 64 x 64 (BN =
+// 128), or 4 x 1 of 32 x 32 (BN = 32) for launches that would leave CUs idle,
+// which have few wavefronts to hide their loads and run them four K steps
+// ahead.
+template <int BN>
 __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
     const uint16_t *__restrict__ S, const uint16_t *__restrict__ D, const float *__restrict__ sn,
     const float *__restrict__ dn, int64_t M, int64_t N, int64_t P, uint32_t *__restrict__ cand,
-    int tiles_m, int tiles_n, int splits, int64_t kchunk, float *__restrict__ partials) {
-  constexpr int kSeg = kBKH / 8;           // 16-byte segments per row and step
-  constexpr int kLoads = kBM * kSeg / 256; // segments per thread and operand
+    int tiles_m, int tiles_n) {
+  constexpr int kSeg = kBKH / 8;                                       // 16-byte segments per row and step
+  constexpr int kA = kBM * kSeg / 256, kB = BN * kSeg / 256;           // segments per thread
+  constexpr int kWaveN = BN == 128 ? 2 : 1, kWaveM = 4 / kWaveN;       // wavefronts of a tile
+  constexpr int kI = kBM / kWaveM / 32, kJ = BN / kWaveN / 32;         // accumulators of a wavefront
+  constexpr int kAhead = BN == 128 ? 1 : 4;
   __shared__ __attribute__((aligned(16))) uint16_t As[kBM * kLdH];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[kBN * kLdH];
-  __shared__ float sns[kBM], dns[kBN];
-  __shared__ uint32_t red[2][kBN][8];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * kLdH];
+  __shared__ float sns[kBM], dns[BN];
+  __shared__ uint32_t red[kWaveM][BN][8];
 
   int tm, tn, split;
-  tile_of_block(tiles_m, tiles_n, splits, tm, tn, split);
-  const int64_t row0 = (int64_t)tm * kBM, col0 = (int64_t)tn * kBN;
+  tile_of_block(tiles_m, tiles_n, 1, tm, tn, split);
+  const int64_t row0 = (int64_t)tm * kBM, col0 = (int64_t)tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, lr = lane & 31, lh = lane >> 5;
-  const int64_t kbeg = (int64_t)split * kchunk, kend = min(P, kbeg + kchunk);
+  const int wm = wave / kWaveN, wn = wave % kWaveN, lr = lane & 31, lh = lane >> 5;
 
-  uint4 ra[kLoads], rb[kLoads];
-  auto gload = [&](int64_t k0) {
+  // rows past the last read the last one: their outputs are not used
+  uint4 ra[kAhead][kA], rb[kAhead][kB];
+  const uint16_t *pa[kA], *pb[kB];
+  const int c = (tid % kSeg) * 8;
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int id = tid + 256 * i, r = id / kSeg, c = (id % kSeg) * 8;
-      ra[i] = load_row8h(S, M, row0 + r, kend, k0 + c, P);
-      rb[i] = load_row8h(D, N, col0 + r, kend, k0 + c, P);
-    }
+  for (int i = 0; i < kA; ++i) pa[i] = S + min(row0 + (tid + 256 * i) / kSeg, M - 1) * P + c;
+#pragma unroll
+  for (int i = 0; i < kB; ++i) pb[i] = D + min(col0 + (tid + 256 * i) / kSeg, N - 1) * P + c;
+  const int whole = (int)(P / kBKH);   // whole K steps
+  auto gload = [&](int step, int set) {   // steps past the last whole one load that
+    const int64_t k = (int64_t)min(step, whole - 1) * kBKH;
+#pragma unroll
+    for (int i = 0; i < kA; ++i) __builtin_memcpy(&ra[set][i], pa[i] + k, 16);
+#pragma unroll
+    for (int i = 0; i < kB; ++i) __builtin_memcpy(&rb[set][i], pb[i] + k, 16);
+  };
+  auto lstore = [&](int set) {
+#pragma unroll
+    for (int i = 0; i < kA; ++i) *reinterpret_cast<uint4 *>(&As[(tid + 256 * i) / kSeg * kLdH + c]) = ra[set][i];
+#pragma unroll
+    for (int i = 0; i < kB; ++i) *reinterpret_cast<uint4 *>(&Bs[(tid + 256 * i) / kSeg * kLdH + c]) = rb[set][i];
   };
 
-  floatx16 acc[2][2];
+  floatx16 acc[kI][kJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < kI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < kJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  gload(kbeg);
-  for (int64_t k0 = kbeg; k0 < kend; k0 += kBKH) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int id = tid + 256 * i, r = id / kSeg, c = (id % kSeg) * 8;
-      *reinterpret_cast<uint4 *>(&As[r * kLdH + c]) = ra[i];
-      *reinterpret_cast<uint4 *>(&Bs[r * kLdH + c]) = rb[i];
-    }
-    __syncthreads();
-    if (k0 + kBKH < kend) gload(k0 + kBKH);
+  auto multiply = [&]() {
 #pragma unroll
     for (int kk = 0; kk < kBKH / 16; ++kk) {
-      bf16x8 a[2], b[2];
+      bf16x8 a[kI], b[kJ];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const bf16x8 *>(&As[(wm * 64 + i * 32 + lr) * kLdH + kk * 16 + lh * 8]);
+      for (int i = 0; i < kI; ++i)
+        a[i] = *reinterpret_cast<const bf16x8 *>(&As[((wm * kI + i) * 32 + lr) * kLdH + kk * 16 + lh * 8]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        b[j] = *reinterpret_cast<const bf16x8 *>(&Bs[(wn * 64 + j * 32 + lr) * kLdH + kk * 16 + lh * 8]);
+      for (int j = 0; j < kJ; ++j)
+        b[j] = *reinterpret_cast<const bf16x8 *>(&Bs[((wn * kJ + j) * 32 + lr) * kLdH + kk * 16 + lh * 8]);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < kI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < kJ; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
+  };
+  auto step = [&](int s, int set) {
+    __syncthreads();
+    lstore(set);
+    gload(s + kAhead, set);
+    __syncthreads();
+    multiply();
+  };
+  if (whole > 0) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) gload(d, d);
+    int s = 0;
+    for (; s + kAhead <= whole; s += kAhead) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) step(s + u, u);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead - 1; ++u)
+      if (s + u < whole) step(s + u, u);
+  }
+  if (P % kBKH) {   // the ragged step
+    const int k0 = whole * kBKH, left = (int)(P - k0) - c;
+#pragma unroll
+    for (int i = 0; i < kA; ++i) ra[0][i] = load_oct(pa[i] + k0, left);
+#pragma unroll
+    for (int i = 0; i < kB; ++i) rb[0][i] = load_oct(pb[i] + k0, left);
+    __syncthreads();
+    lstore(0);
+    __syncthreads();
+    multiply();
   }
 
-  if (splits > 1) {
-    float *mine = partials + ((int64_t)(tm * tiles_n + tn) * splits + split) * (kBM * kBN);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          mine[(wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * kBN + wn * 64 + j * 32 + lr] =
-              acc[i][j][r];
-    return;
-  }
   if (tid < kBM) {
     sns[tid] = row0 + tid < M ? sn[row0 + tid] : 0.f;
-  } else {
-    const int c = tid - kBM;
-    dns[c] = col0 + c < N ? dn[col0 + c] : 0.f;
+  } else if (tid < kBM + BN) {
+    const int cl = tid - kBM;
+    dns[cl] = col0 + cl < N ? dn[col0 + cl] : 0.f;
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int cl = wn * 64 + j * 32 + lr;
+  for (int j = 0; j < kJ; ++j) {
+    const int cl = (wn * kJ + j) * 32 + lr;
     uint32_t top[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) top[s] = ~0u;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int rl = wm * 64 + i * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
+        const int rl = (wm * kI + i) * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
         if (row0 + rl < M) {
           const float b = fmaf(-2.0f, acc[i][j][r], sns[rl] + dns[cl]);
           insert8(top, (float_key(b) & ~127u) | (uint32_t)rl);
@@ -589,51 +615,15 @@ __global__ __launch_bounds__(256, 2) void match_bf16_kernel(
     }
   }
   __syncthreads();
-  if (tid < kBN && col0 + tid < N) {
+  if (tid < BN && col0 + tid < N) {
     uint32_t top[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) top[s] = red[0][tid][s];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) insert8(top, red[1][tid][s]);
+    for (int w = 1; w < kWaveM; ++w)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) insert8(top, red[w][tid][s]);
     uint4 *dst = reinterpret_cast<uint4 *>(cand + ((int64_t)tm * N + col0 + tid) * 8);
-    dst[0] = make_uint4(top[0], top[1], top[2], top[3]);
-    dst[1] = make_uint4(top[4], top[5], top[6], top[7]);
-  }
-}
-
-// Epilogue of a split launch: per-tile column top-8 of the summed partials
-// (threads as in reduce_f32_kernel).
-__global__ __launch_bounds__(256) void reduce_bf16_kernel(
-    const float *__restrict__ partials, int splits, const float *__restrict__ sn,
-    const float *__restrict__ dn, int64_t M, int64_t N, int tiles_n, uint32_t *__restrict__ cand) {
-  constexpr int kGroups = 256 / kRedCols;
-  __shared__ uint32_t red[kGroups][kRedCols][9];
-  const int tile = blockIdx.x / (kBN / kRedCols), c0 = (blockIdx.x % (kBN / kRedCols)) * kRedCols;
-  const int cl = threadIdx.x & (kRedCols - 1), rg = threadIdx.x / kRedCols;
-  const int tm = tile / tiles_n;
-  const int64_t row0 = (int64_t)tm * kBM, n = (int64_t)(tile % tiles_n) * kBN + c0 + cl;
-  const float *part = partials + (int64_t)tile * splits * (kBM * kBN);
-  uint32_t top[8];
-#pragma unroll
-  for (int s = 0; s < 8; ++s) top[s] = ~0u;
-  if (n < N) {
-    const float dnn = dn[n];
-#pragma unroll 4
-    for (int j = 0; j < kRedRows; ++j) {
-      const int row = rg * kRedRows + j;
-      if (row0 + row >= M) break;
-      const float b = fmaf(-2.0f, split_sum(part, splits, row, c0 + cl), sn[row0 + row] + dnn);
-      insert8(top, (float_key(b) & ~127u) | (uint32_t)row);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 8; ++s) red[rg][cl][s] = top[s];
-  __syncthreads();
-  if (rg == 0 && n < N) {
-    for (int k = 1; k < kGroups; ++k)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) insert8(top, red[k][cl][s]);
-    uint4 *dst = reinterpret_cast<uint4 *>(cand + ((int64_t)tm * N + n) * 8);
     dst[0] = make_uint4(top[0], top[1], top[2], top[3]);
     dst[1] = make_uint4(top[4], top[5], top[6], top[7]);
   }
@@ -831,14 +821,28 @@ __global__ __launch_bounds__(512, 1) void match_bf16_big_kernel(
   }
 }
 
-size_t match_bf16_partial_bytes(int64_t M, int64_t N, int64_t P) {
-  const int s = bf16_splits(M, N, P);
-  return s > 1 ? (size_t)tiles_of(M, N, kBM) * s * kBM * kBN * sizeof(float) : 0;
+// Tiles of 32 images instead of 128 up to this many 128 x 128 tiles (half a
+// tile per CU).  Whole calls, 128 and 32 images: 1 tile (100 x 32 x 4,096) 92
+// and 61 us; 2 (200 x 64 x 25,600) 329 and 176; 16 (1,000 x 256 x 4,096) 98
+// and 66; 32 (1,000 x 512 x 10,089) 197 and 129; 128 (2,000 x 1,000 x 4,096)
+// 100 and 86; 144 (1,500 x 1,500 x 4,096) 107 and 110; 240 (2,048 x 1,900 x
+// 3,000) 98 and 125.
+constexpr int64_t kNarrowTiles = 128;
+
+template <int BN>
+static hipError_t match_bf16_go(const uint16_t *S, const uint16_t *D, const float *sn, const float *dn,
+                                int64_t M, int64_t N, int64_t P, uint32_t *cand, hipStream_t s) {
+  const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + BN - 1) / BN);
+  const int64_t blocks = (int64_t)tiles_m * tiles_n;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((match_bf16_kernel<BN>), dim3((unsigned)blocks), dim3(256), 0, s, S, D, sn, dn, M,
+                     N, P, cand, tiles_m, tiles_n);
+  return hipGetLastError();
 }
 
 hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *sn,
                              const float *dn, int64_t M, int64_t N, int64_t P, uint32_t *cand,
-                             float *partials, hipStream_t s) {
+                             hipStream_t s) {
   if (match_bf16_tile_rows(M, N, P, S, D) == 256) {
     const int tiles_m = (int)((M + kBM2 - 1) / kBM2), tiles_n = (int)((N + kBN2 - 1) / kBN2);
     const int64_t blocks = (int64_t)tiles_m * tiles_n;
@@ -847,17 +851,8 @@ hipError_t launch_match_bf16(const uint16_t *S, const uint16_t *D, const float *
                        dn, M, N, P, cand, tiles_m, tiles_n);
     return hipGetLastError();
   }
-  const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-  const int splits = bf16_splits(M, N, P);
-  const int64_t tiles = (int64_t)tiles_m * tiles_n, blocks = tiles * splits;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const int64_t kchunk = ((P + splits - 1) / splits + kBKH - 1) / kBKH * kBKH;
-  hipLaunchKernelGGL(match_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, S, D, sn, dn, M,
-                     N, P, cand, tiles_m, tiles_n, splits, kchunk, partials);
-  if (splits > 1)
-    hipLaunchKernelGGL(reduce_bf16_kernel, dim3((unsigned)(tiles * (kBN / kRedCols))), dim3(256), 0, s,
-                       partials, splits, sn, dn, M, N, tiles_n, cand);
-  return hipGetLastError();
+  return tiles_of(M, N, kBM) <= kNarrowTiles ? match_bf16_go<32>(S, D, sn, dn, M, N, P, cand, s)
+                                             : match_bf16_go<kBN>(S, D, sn, dn, M, N, P, cand, s);
 }
 
 // Bounds of the certified rescore (float32 arithmetic; every bound carries

@@ -1,9 +1,9 @@
-"""Matcher launches that split K over blocks (few tiles) and rows at every
-alignment (row lengths that are not a multiple of 4 or 8), against the
-oracle's float64 distances.  Images are Poisson counts of picked rows, so
-almost every image is decided; the distance bounds are the documented chains (FP32:
-36 + ceil(P/32) roundings of the expanded form, BF16: P/64 + 16 of the direct
-sum)."""
+"""Matcher launches of few tiles (FP32: tiles of 64 and K split over blocks;
+BF16: tiles of 32 images) and rows at every alignment (row lengths that are
+not a multiple of 4 or 8), against the oracle's float64 distances.  Images are
+Poisson counts of picked rows, so almost every image is decided; the distance
+bounds are the documented chains (FP32: 36 + ceil(P/32) roundings of the
+expanded form, BF16: P/64 + 16 of the direct sum)."""
 import numpy as np
 import pytest
 import torch
@@ -15,14 +15,14 @@ from tests._common import DEV, gpu, host
 pytestmark = pytest.mark.gpu
 
 
-# one tile at 1 and at 128 rows and images, one past, P below one split's
-# length (unsplit), at and just past two, ragged by 1, 2 and 7, more splits
-# than whole K steps per split divide evenly, a launch past half a round of
-# 128-row tiles (unsplit), and launches of 256-row tiles (144 of
-# them) and just below (136: 128-row tiles)
+# one tile at 1 and at 128 rows and images, one past, P below the split length
+# of 1,024 (unsplit), at and just past two splits, ragged by 1, 2 and 7, whole
+# K steps that the splits do not divide evenly, a launch of 289 128-row tiles,
+# and BF16 launches on both sides of the 256-row tiles' range (136, 144 and 306
+# of them)
 @pytest.mark.parametrize("M,N,P", [
     (1, 1, 1024), (3, 2, 1023), (128, 128, 1025), (129, 127, 1030), (257, 130, 5121),
-    (300, 40, 8199), (64, 200, 16390), (40, 9, 511), (2100, 2050, 700), (300, 17400, 64), (4400, 1990, 64),
+    (300, 40, 8199), (64, 200, 16390), (40, 9, 511), (2100, 2050, 700), (300, 17400, 64), (4400, 1990, 64), (4100, 4400, 64),
 ])
 @pytest.mark.parametrize("mode", [spfel.MATCH_FP32, spfel.MATCH_BF16_RESCORE8])
 def test_split_and_ragged_launches(mode, M, N, P):
