@@ -64,10 +64,9 @@ struct DftEpilogue {
   const float *lambda = nullptr;   // host values, one per system
   int systems = 0;
   int64_t cols_per_system = 0;
-  // real-space step of phasing (kCyclic, kHR): out is rho, updated in place
+  // real-space step of error reduction (kCyclic, kHR): out is rho
   const uint8_t *support = nullptr;
-  int hio = 0, positivity = 0;
-  float beta = 0.f;
+  int positivity = 0;
   // error of a phasing iteration (kCyclic, kCC): *err = sum of the first
   // err_n partial sums over the sum of the next err_n, by the first block
   const float *err_part = nullptr;

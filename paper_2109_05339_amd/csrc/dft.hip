@@ -26,8 +26,8 @@
 // Measured on an application of the normal equations (N = 129, L = 258, 8
 // REAL systems): 7.1 ms by full complex tables (42% of the FP32 matrix rate
 // on eleven times the products), 0.72 ms here: axis-0 pass 312 us, axis 1
-// 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.  One phasing
-// iteration at N = 129: 329 us by full tables and full spectra, 70 us here
+// 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.  One error
+// reduction at N = 129: 329 us by full tables and full spectra, 70 us here
 // (axis-0 pass with the projection 26 us, the others 11 to 13 us each, half
 // of it matrix instructions).  The merge's transform at N = 129: 515 us plus a
 // 17 us clear of the accumulator by full tables, 79 us here.
@@ -381,8 +381,7 @@ struct Tail {
   float lambda[kMaxLambdas];
   uint32_t per;   // columns per system
   const uint8_t *support;
-  int hio, positivity;
-  float beta;
+  int positivity;
   const float *err_part;
   int err_n;
   float *err;
@@ -555,9 +554,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
       auto put = [&](int e, float y) {
         const uint32_t o = base + (uint32_t)e * st;
         if constexpr (KIND == kCyclic) {
-          if (tail.support) {   // the real-space step of phasing
+          if (tail.support) {   // the real-space step of error reduction
             const bool holds = tail.support[o] && (!tail.positivity || y >= 0.f);
-            y = holds ? y : (tail.hio ? fmaf(-tail.beta, y, out[o]) : 0.f);
+            y = holds ? y : 0.f;
           }
         } else {
           if (tail.lam_v)
@@ -969,9 +968,7 @@ hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const voi
   for (int i = 0; i < ep.systems && i < kMaxLambdas; ++i) t.lambda[i] = ep.lambda[i];
   t.per = ep.cols_per_system > 0 ? ep.cols_per_system : 1;
   t.support = ep.support;
-  t.hio = ep.hio;
   t.positivity = ep.positivity;
-  t.beta = ep.beta;
   t.err_part = ep.err_part;
   t.err_n = ep.err_n;
   t.err = ep.err;

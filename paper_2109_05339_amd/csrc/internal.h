@@ -105,12 +105,12 @@ void kernel_transform(int N, int nf, int w, double beta, double *out);
 constexpr int kMaxPartials = 1024;
 
 // ---- launchers (return hipSuccess or the launch error) ----
-// Y[a][k][b] = sum_l X[a][l][b] W[l][k] (X float or float2 per x_complex);
-// out_mode: 0 store float2, 1 store real part (float), 2 add real part,
-// 3 add float2.
-hipError_t launch_contract(const void *X, bool x_complex, const float2 *W,
-                           void *Y, int out_mode, int A, int L, int K, int B,
-                           hipStream_t s);
+// Y[a][k][b] = sum_l X[a][l][b] W[l][k] (real_out: its real part, as float),
+// and the same over the rows of X (b = 0 alone; X float or float2).
+hipError_t launch_contract(const float2 *X, const float2 *W, void *Y, bool real_out, int A, int L,
+                           int K, int B, hipStream_t s);
+hipError_t launch_contract_rows(const void *X, bool x_complex, const float2 *W, float2 *Y, int A, int L,
+                                int K, hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
 // detq == nullptr selects the plan's registered detector (tiled kernel).

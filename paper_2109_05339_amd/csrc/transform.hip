@@ -1,8 +1,5 @@
-// Separable transforms between the N^3 model modes and the 2N-per-axis fine
-// grid.  The zero-padded 3D FFT plus kernel deconvolution of an ES-kernel
-// NUFFT is applied one axis at a time as a contraction with a small table
-// W[l][k] = exp(+-2 pi i k l / nf) / psi_hat(k): padding and truncation fold
-// into the table's shape, and the deconvolution into its rows.
+// Contraction of one axis of an array with a small full table: the transforms
+// of HIO phasing and the passes of the shrinkwrap blur.
 #include "internal.h"
 
 namespace spfel {
@@ -10,8 +7,8 @@ namespace spfel {
 // Y[a][k][b] = sum_l X[a][l][b] W[l][k] on the matrix cores, as a complex
 // GEMM per batch z:
 // C[m][n] = sum_l P[m][l] Q[l][n] with element strides (a real operand has
-// zero imaginary parts).  B = 1: P = X (rows a), Q = W, C = Y.  B > 1:
-// P = W^T, Q = X[a] (one batch per a), C = Y[a].  Block tiles of 64 x 64
+// zero imaginary parts).  Rows (B = 1): P = X (rows a), Q = W, C = Y;
+// otherwise P = W^T, Q = X[a] (one batch per a), C = Y[a].  Block tiles of 64 x 64
 // complex outputs (four wavefronts of 32 x 32, 2 x 2 v_mfma_f32_16x16x4f32
 // tiles each, real and imaginary accumulators), K steps of 8 complex l
 // staged in LDS.  One instruction takes K = 4 real terms, i.e. 2 complex l
@@ -23,10 +20,10 @@ namespace spfel {
 constexpr int kCM = 64, kCN = 64, kCK = 8;
 typedef float cfx4 __attribute__((ext_vector_type(4)));
 
-template <bool PR, bool QR, int OUT, bool PUNIT_M>
+template <bool PR, bool REAL_OUT, bool PUNIT_M>
 __global__ __launch_bounds__(256) void contract_mfma_kernel(
     const void *__restrict__ P_, int64_t psm, int64_t psl, int64_t psz,
-    const void *__restrict__ Q_, int64_t qsl, int64_t qsz, void *__restrict__ C_, int64_t csm,
+    const float2 *__restrict__ Q, int64_t qsl, int64_t qsz, void *__restrict__ C_, int64_t csm,
     int64_t csz, int M, int N, int L, int tiles_m, int tiles_n) {
   __shared__ float2 Ps[kCK][kCM];
   __shared__ float2 Qs[kCK][kCN];
@@ -48,9 +45,7 @@ __global__ __launch_bounds__(256) void contract_mfma_kernel(
   };
   auto loadQ = [&](int l, int n) -> float2 {
     if (n >= N || l >= L) return make_float2(0.f, 0.f);
-    const int64_t o = z * qsz + (int64_t)l * qsl + n;
-    if (QR) return make_float2(static_cast<const float *>(Q_)[o], 0.f);
-    return static_cast<const float2 *>(Q_)[o];
+    return Q[z * qsz + (int64_t)l * qsl + n];
   };
 
   cfx4 accr[2][2], acci[2][2];
@@ -116,59 +111,44 @@ __global__ __launch_bounds__(256) void contract_mfma_kernel(
         if (m >= M || n >= N) continue;
         const int64_t o = z * csz + (int64_t)m * csm + n;
         const float re = accr[a][b][j], im = acci[a][b][j];
-        if (OUT == 0) {
-          static_cast<float2 *>(C_)[o] = make_float2(re, im);
-        } else if (OUT == 1) {
+        if (REAL_OUT)
           static_cast<float *>(C_)[o] = re;
-        } else if (OUT == 2) {
-          static_cast<float *>(C_)[o] += re;
-        } else {
-          float2 *C = static_cast<float2 *>(C_);
-          const float2 y = C[o];
-          C[o] = make_float2(y.x + re, y.y + im);
-        }
+        else
+          static_cast<float2 *>(C_)[o] = make_float2(re, im);
       }
 }
 
-template <bool PR, bool QR, bool PUNIT_M>
+template <bool PR, bool PUNIT_M>
 static hipError_t contract_mfma(const void *P, int64_t psm, int64_t psl, int64_t psz,
-                                const void *Q, int64_t qsl, int64_t qsz, void *C, int64_t csm,
-                                int64_t csz, int M, int N, int L, int64_t batch, int out_mode,
+                                const float2 *Q, int64_t qsl, int64_t qsz, void *C, int64_t csm,
+                                int64_t csz, int M, int N, int L, int64_t batch, bool real_out,
                                 hipStream_t s) {
   const int tiles_m = (M + kCM - 1) / kCM, tiles_n = (N + kCN - 1) / kCN;
   const int64_t blocks = batch * tiles_m * tiles_n;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(256);
-#define SPFEL_CMFMA(O)                                                                      \
-  hipLaunchKernelGGL((contract_mfma_kernel<PR, QR, O, PUNIT_M>), grid, block, 0, s, P, psm, \
-                     psl, psz, Q, qsl, qsz, C, csm, csz, M, N, L, tiles_m, tiles_n)
-  switch (out_mode) {
-    case 0: SPFEL_CMFMA(0); break;
-    case 1: SPFEL_CMFMA(1); break;
-    case 2: SPFEL_CMFMA(2); break;
-    default: SPFEL_CMFMA(3); break;
-  }
-#undef SPFEL_CMFMA
+  if (real_out)
+    hipLaunchKernelGGL((contract_mfma_kernel<PR, true, PUNIT_M>), grid, block, 0, s, P, psm, psl,
+                       psz, Q, qsl, qsz, C, csm, csz, M, N, L, tiles_m, tiles_n);
+  else
+    hipLaunchKernelGGL((contract_mfma_kernel<PR, false, PUNIT_M>), grid, block, 0, s, P, psm, psl,
+                       psz, Q, qsl, qsz, C, csm, csz, M, N, L, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
-hipError_t launch_contract(const void *X, bool x_complex, const float2 *W, void *Y,
-                           int out_mode, int A, int L, int K, int B, hipStream_t s) {
+hipError_t launch_contract_rows(const void *X, bool x_complex, const float2 *W, float2 *Y, int A, int L,
+                                int K, hipStream_t s) {
+  if ((int64_t)A * K == 0) return hipSuccess;
+  return x_complex ? contract_mfma<false, false>(X, L, 1, 0, W, K, 0, Y, K, 0, A, K, L, 1, false, s)
+                   : contract_mfma<true, false>(X, L, 1, 0, W, K, 0, Y, K, 0, A, K, L, 1, false, s);
+}
+
+hipError_t launch_contract(const float2 *X, const float2 *W, void *Y, bool real_out, int A, int L,
+                           int K, int B, hipStream_t s) {
   if ((int64_t)A * K * B == 0) return hipSuccess;
-  if (B == 1) {
-    // rows a of X against W: P = X (A x L), Q = W (L x K)
-    return x_complex
-               ? contract_mfma<false, false, false>(X, L, 1, 0, W, K, 0, Y, K, 0, A, K, L, 1,
-                                                    out_mode, s)
-               : contract_mfma<true, false, false>(X, L, 1, 0, W, K, 0, Y, K, 0, A, K, L, 1,
-                                                   out_mode, s);
-  }
   // per a: W^T (K x L) against X[a] (L x B)
-  return x_complex
-             ? contract_mfma<false, false, true>(W, 1, K, 0, X, B, (int64_t)L * B, Y, B,
-                                                 (int64_t)K * B, K, B, L, A, out_mode, s)
-             : contract_mfma<false, true, true>(W, 1, K, 0, X, B, (int64_t)L * B, Y, B,
-                                                (int64_t)K * B, K, B, L, A, out_mode, s);
+  return contract_mfma<false, true>(W, 1, K, 0, X, B, (int64_t)L * B, Y, B, (int64_t)K * B, K, B, L,
+                                    A, real_out, s);
 }
 
 // Zero fill with a kernel (kept out of memset nodes so callers may capture
