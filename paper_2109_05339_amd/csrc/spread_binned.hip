@@ -667,6 +667,8 @@ static hipError_t spread_binned_wc(const Plan &pl, const float *quats, int64_t n
   const bool two = n_img > pl.bin_batch;
   hipStream_t bs = two ? pl.bin_stream : s;
   hipError_t e = hipSuccess;
+  const bool recorded = capturing(s);
+  if (recorded) pl.bin_zero = false;
   if (two) {
     e = hipEventRecord(pl.ev_bin_start, s);
     if (e == hipSuccess) e = hipStreamWaitEvent(bs, pl.ev_bin_start, 0);
@@ -712,6 +714,7 @@ static hipError_t spread_binned_wc(const Plan &pl, const float *quats, int64_t n
     if (e == hipSuccess && two) e = hipEventRecord(pl.ev_spread[k], s);
     if (e != hipSuccess) return e;
   }
+  if (recorded) pl.bin_zero = false;
   return hipSuccess;
 }
 

@@ -60,3 +60,31 @@ def test_crowded_bins(w, real):
     # 40 x 400 points within two cells of the origin: a few bins of
     # thousands of points each, cut into several subproblems
     check(13, w, real, 40, 20, 0.08)
+
+
+@pytest.mark.parametrize("domain", [spfel.REAL, spfel.COMPLEX])
+def test_recorded_merges_do_not_count_as_run(domain):
+    """A plan keeps its accumulator and bin counts cleared between merges.  A
+    merge that is captured has not run: an eager one right after the capture,
+    before any replay, and replays between eager ones give the same sums."""
+    det = synth.detector_q(24).astype(np.float32)
+    q = gpu(synth.quaternions(synth.config(4), "image_quats", 9))
+    dtype = torch.float32 if domain == spfel.REAL else torch.complex64
+    v = gpu(np.random.default_rng(3).standard_normal((9, len(det))), dtype)
+    other = spfel.Plan(25, domain=domain, device=DEV)   # loads the kernels before the capture
+    other.set_detector(gpu(det))
+    ref = host(other.merge_adjoint(q, None, v))
+    plan = spfel.Plan(25, domain=domain, device=DEV)
+    plan.set_detector(gpu(det))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = plan.merge_adjoint(q, None, v)
+    eager = [host(plan.merge_adjoint(q, None, v))]
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        eager.append(host(out.clone()))
+        eager.append(host(plan.merge_adjoint(q, None, v)))
+    for got in eager:   # float atomics in any order: a few roundings per cell
+        assert rel(got, ref) <= 1e-5
