@@ -267,8 +267,8 @@ int spfel_orient(spfel_plan plan, const float *quats, int64_t M,
  *                           with DEFER).
  * Spreading uses float32 atomics, so the summation order (and the last bits
  * of the result) can vary between runs.  With the registered detector the
- * points are binned in batches of up to 2^27 on a stream the plan owns
- * (ordered after the work already on `stream`, and before the work queued
+ * points are binned in batches of up to 2^27; where there are several, on a
+ * stream the plan owns (ordered after the work already on `stream`, and before the work queued
  * on `stream` after this call) while the previous batch spreads on
  * `stream`. */
 int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
@@ -378,9 +378,8 @@ int spfel_normal_lcurve(spfel_normal nm, const void *x, const void *rhs,
  * Shrinkwrap replaces the support by the cells where the periodic Gaussian
  * blur (standard deviation sigma cells, unit sum, separable circular
  * convolution) of |rho| reaches tau times its maximum.
- * The transforms are separable line transforms (float32).  An spfel_phase
- * object holds the tables and intermediates for one N (24 to 28 N^3 bytes,
- * allocated at create; later calls allocate nothing); calls on one object
+ * The transforms are separable (float32).  An spfel_phase object holds the
+ * tables and intermediates for one N (28 N^3 bytes, allocated at create; later calls allocate nothing); calls on one object
  * share them, so work on different streams must not overlap. */
 
 /* n in 2..1024 cells per axis, on HIP device `device`. */

@@ -223,7 +223,7 @@ static size_t alloc_bins(Plan *p, int64_t P) {
 
 static void free_plan(Plan *p) {
   free_bins(p);
-  void *bufs[] = {p->u, p->to_grid.t, p->to_modes.t, p->t1, p->t2, p->acc, p->partials, p->rot,
+  void *bufs[] = {p->u, p->wpos, p->to_modes.t, p->t1, p->t2, p->acc, p->partials, p->rot,
                   p->det_sorted, p->det_perm};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
@@ -292,14 +292,14 @@ int spfel_plan_create(spfel_plan *out, int n_model, int kernel_width,
   const size_t N = n_model, nf = p->nf;
   const size_t el = domain == SPFEL_COMPLEX ? sizeof(float2) : sizeof(float);
   const size_t grid_b = nf * nf * nf * el;
-  const size_t tab_grid = dft_table_sizes(p->to_grid, kToGrid, (n_model - 1) / 2, n_model);
+  const size_t tab_grid = N * nf * sizeof(float2);
   const size_t tab_modes = dft_table_sizes(p->to_modes, kToModes, (n_model - 1) / 2, n_model);
   const size_t tmp_b = 4 * N * N * N * sizeof(float2);
   struct Req {
     void **ptr;
     size_t bytes;
   } reqs[] = {{&p->u, grid_b},
-              {reinterpret_cast<void **>(&p->to_grid.t), tab_grid},
+              {reinterpret_cast<void **>(&p->wpos), tab_grid},
               {reinterpret_cast<void **>(&p->to_modes.t), tab_modes},
               {reinterpret_cast<void **>(&p->t1), tmp_b},
               {reinterpret_cast<void **>(&p->t2), tmp_b},
@@ -343,7 +343,20 @@ int spfel_plan_create(spfel_plan *out, int n_model, int kernel_width,
   std::vector<double> ph(N);
   kernel_transform(n_model, p->nf, kernel_width, p->beta, ph.data());
   const auto deconvolve = [&](int k) { return 1.0 / ph[(n_model - 1) / 2 + k]; };
-  e = dft_table_fill(p->to_grid, +1, true, deconvolve);
+  // The table of the model -> grid transform in float64, rounded once; the
+  // phase index is reduced modulo nf exactly.  Index l is cell l - nf/2.
+  std::vector<float2> wp(N * nf);
+  for (int ki = 0; ki < n_model; ++ki) {
+    const long k = ki - (n_model - 1) / 2;
+    for (int l = 0; l < p->nf; ++l) {
+      const long nl = (long)nf;
+      long rc = (k * ((long)l - nl / 2)) % nl;
+      if (rc < 0) rc += nf;
+      const double ac = 2.0 * M_PI * (double)rc / (double)nf;
+      wp[(size_t)ki * nf + l] = make_float2((float)(std::cos(ac) / ph[ki]), (float)(std::sin(ac) / ph[ki]));
+    }
+  }
+  e = hipMemcpy(p->wpos, wp.data(), tab_grid, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = dft_table_fill(p->to_modes, -1, false, deconvolve);
   if (e != hipSuccess) {
     free_plan(p);
@@ -505,17 +518,13 @@ int spfel_set_model(spfel_plan plan, const void *model, void *stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int N = p->N, nf = p->nf;
   // u[l] = sum_k m_k exp(+2 pi i k.l / nf) / (psi_hat psi_hat psi_hat), one
-  // axis at a time: axis 2 (N^2 lines), axis 1, axis 0.  A real model's sum is
-  // Hermitian: its nonnegative half along axis 2 is enough until the last
-  // pass, which writes the real part at each cell and at its mirror image.
-  const int half = cplx ? nf : N + 1;
-  DftEpilogue none, last;
-  last.mirror1 = last.mirror2 = nf;
-  hipError_t e = launch_dft(p->to_grid, cplx ? kCC : kRH, {(int64_t)N * N, 1, N, half}, model, p->t1, none, s);
-  if (e == hipSuccess)
-    e = launch_dft(p->to_grid, kCC, {(int64_t)N * half, half, N, nf}, p->t1, p->t2, none, s);
-  if (e == hipSuccess)
-    e = launch_dft(p->to_grid, cplx ? kCC : kCRe, {(int64_t)nf * half, nf * half, N, nf}, p->t2, p->u, last, s);
+  // axis at a time: axis 2 (N^2 lines), axis 1, axis 0.  By full tables: the
+  // grid's rounding reaches the distances of orientation matching, differences
+  // of nearly equal sums, some five hundred times larger (line transforms, 0.10
+  // instead of 0.37 ms at N = 129, moved them by 5e-5 of themselves).
+  hipError_t e = launch_contract_rows(model, cplx, p->wpos, p->t1, N * N, N, nf, s);
+  if (e == hipSuccess) e = launch_contract(p->t1, p->wpos, p->t2, false, N, N, nf, nf, s);
+  if (e == hipSuccess) e = launch_contract(p->t2, p->wpos, p->u, !cplx, 1, N, nf, nf * nf, s);
   if (e != hipSuccess) return hip_fail(e, "set_model: launch");
   p->model_set = true;
   return SPFEL_OK;
@@ -824,7 +833,8 @@ int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
   const size_t nf = p->nf;
   const size_t grid_b = nf * nf * nf * (cplx ? sizeof(float2) : sizeof(float));
   hipError_t e = hipSuccess;
-  if (!p->pending && !p->acc_zero) e = launch_fill_zero(p->acc, grid_b, s);
+  const bool recorded = capturing(s);
+  if (!p->pending && (recorded || !p->acc_zero)) e = launch_fill_zero(p->acc, grid_b, s);
   p->acc_zero = false;
   if (e == hipSuccess && any) e = launch_spread(*p, quats, n_img, det_q, P, values, weights, s);
   if (e != hipSuccess) return hip_fail(e, "merge_adjoint: launch");
@@ -843,7 +853,7 @@ int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
   last.accumulate = (flags & SPFEL_MERGE_ACCUMULATE) != 0;
   last.mirror1 = last.mirror2 = N;
   e = launch_dft(p->to_modes, cplx ? kCC : kRH, {(int64_t)nfi * nfi, 1, nfi, half}, p->acc, p->t1, first, s);
-  p->acc_zero = e == hipSuccess;
+  p->acc_zero = e == hipSuccess && !recorded;
   if (e == hipSuccess)
     e = launch_dft(p->to_modes, kCC, {(int64_t)nfi * half, half, nfi, N}, p->t1, p->t2, none, s);
   if (e == hipSuccess)

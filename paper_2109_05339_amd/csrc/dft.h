@@ -1,6 +1,6 @@
 // Line transforms of the separable 3D DFTs (dft.hip): tables, shapes and
-// launchers shared by the transforms of slicing and merging, the normal
-// equations and phasing.
+// launchers shared by the merge's transform, the normal equations and
+// phasing.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -22,7 +22,7 @@ enum DftKind { kToGrid = 0, kToModes = 1, kCyclic = 2 };
 //   kRH  real -> complex, the nonnegative half of the output alone
 //        (grid 0..H, modes 0..h, frequencies 0..n/2)
 //   kCRe complex -> the real part, written at the output and at its mirror
-//        image through the origin of the 3D output
+//        image through the origin of the 3D output (kToModes)
 //   kHR  the nonnegative half of a Hermitian line -> real
 enum DftIo { kCC = 0, kRH = 1, kCRe = 2, kHR = 3 };
 

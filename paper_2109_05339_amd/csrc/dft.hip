@@ -523,32 +523,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
       const int i1 = (int)(c / (uint32_t)tail.half), i2 = (int)(c - (uint32_t)i1 * tail.half);
       const int m1 = tail.mirror1, m2 = tail.mirror2;
       auto put1 = [&](uint32_t o, float y) {
-        if (KIND == kToModes && tail.accumulate) y += out[o];
+        if (tail.accumulate) y += out[o];
         out[o] = y;
       };
       auto put = [&](int e, float y) {
-        if constexpr (KIND == kToGrid) {
-          put1(((uint32_t)e * m1 + i1) * m2 + i2, y);
-          if (i2 != 0 && 2 * i2 != m2) {
-            const int f = e == 0 ? 0 : 2 * H - e;
-            put1(((uint32_t)f * m1 + (i1 == 0 ? 0 : m1 - i1)) * m2 + (m2 - i2), y);
-          }
-        } else {
-          put1(((uint32_t)e * m1 + i1) * m2 + h + i2, y);
-          if (i2 != 0) put1(((uint32_t)(2 * h - e) * m1 + (m1 - 1 - i1)) * m2 + h - i2, y);
-        }
+        put1(((uint32_t)e * m1 + i1) * m2 + h + i2, y);
+        if (i2 != 0) put1(((uint32_t)(2 * h - e) * m1 + (m1 - 1 - i1)) * m2 + h - i2, y);
       };
-      if constexpr (KIND == kToGrid) {
-        put(q, a.c - a.s);
-        put(H - q, b.c - b.s);
-        if (q > 0) {
-          put(2 * H - q, a.c + a.s);
-          put(H + q, b.c + b.s);
-        }
-      } else {
-        put(h + q, a.c - a.s);
-        if (q > 0) put(h - q, a.c + a.s);
-      }
+      put(h + q, a.c - a.s);
+      if (q > 0) put(h - q, a.c + a.s);
     } else {   // kHR
       float *out = static_cast<float *>(out_);
       auto put = [&](int e, float y) {
@@ -975,7 +958,6 @@ hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const voi
   switch (tab.kind * 4 + io) {
     case kToGrid * 4 + kCC: return dft_go<kToGrid, kCC>(tab, ln, in, out, t, s);
     case kToGrid * 4 + kRH: return dft_go<kToGrid, kRH>(tab, ln, in, out, t, s);
-    case kToGrid * 4 + kCRe: return dft_go<kToGrid, kCRe>(tab, ln, in, out, t, s);
     case kToModes * 4 + kCC: return dft_go<kToModes, kCC>(tab, ln, in, out, t, s);
     case kToModes * 4 + kRH: return dft_go<kToModes, kRH>(tab, ln, in, out, t, s);
     case kToModes * 4 + kCRe: return dft_go<kToModes, kCRe>(tab, ln, in, out, t, s);

@@ -24,10 +24,11 @@ struct Plan {
   // Fine grid the interpolation reads: nf^3 float (REAL) or float2
   // (COMPLEX), centred storage: cell l at index (l + nf/2) mod nf per axis.
   void *u = nullptr;
-  // Line transforms between the modes and the fine grid:
-  //   to_grid: exp(+2 pi i k (l - nf/2) / nf) / psi_hat(k)  (model -> centred grid)
-  //   to_modes: exp(-2 pi i k l / nf) / psi_hat(k)          (grid -> modes)
-  DftTable to_grid, to_modes;
+  // Transforms between the modes and the fine grid:
+  //   wpos: [N][nf] exp(+2 pi i k (l - nf/2) / nf) / psi_hat(k)  (model -> centred grid)
+  //   to_modes: lines, exp(-2 pi i k l / nf) / psi_hat(k)        (grid -> modes)
+  float2 *wpos = nullptr;
+  DftTable to_modes;
   // Intermediates of the separable transforms, 4 N^3 float2 each.
   float2 *t1 = nullptr;
   float2 *t2 = nullptr;
@@ -112,6 +113,9 @@ hipError_t launch_contract(const float2 *X, const float2 *W, void *Y, bool real_
 hipError_t launch_contract_rows(const void *X, bool x_complex, const float2 *W, float2 *Y, int A, int L,
                                 int K, hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+// Whether work on s is being captured: recorded work has not run, so what the
+// host knows of a buffer's contents holds neither for it nor after it.
+bool capturing(hipStream_t s);
 
 // detq == nullptr selects the plan's registered detector (tiled kernel).
 hipError_t launch_interp(const Plan &pl, const float *quats, int64_t M,

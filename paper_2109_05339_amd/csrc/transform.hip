@@ -1,5 +1,6 @@
-// Contraction of one axis of an array with a small full table: the transforms
-// of HIO phasing and the passes of the shrinkwrap blur.
+// Contraction of one axis of an array with a small full table: the model ->
+// grid transform of slicing, the transforms of HIO phasing and the passes of the
+// shrinkwrap blur.
 #include "internal.h"
 
 namespace spfel {
@@ -166,6 +167,15 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
                      static_cast<uint32_t *>(p), n);
   return hipGetLastError();
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 }  // namespace spfel
