@@ -836,6 +836,11 @@ int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
   const bool recorded = capturing(s);
   if (!p->pending && (recorded || !p->acc_zero)) e = launch_fill_zero(p->acc, grid_b, s);
   p->acc_zero = false;
+  // Until its transform is queued, a recorded merge is one that leaves sums
+  // behind: the host does not see its graph's replays, so from a recorded
+  // deferred merge on the plan's merges fill the accumulator as they begin.
+  const bool replays = p->acc_replays;
+  if (recorded) p->acc_replays = true;
   if (e == hipSuccess && any) e = launch_spread(*p, quats, n_img, det_q, P, values, weights, s);
   if (e != hipSuccess) return hip_fail(e, "merge_adjoint: launch");
   p->pending = true;
@@ -853,7 +858,8 @@ int spfel_merge_adjoint(spfel_plan plan, const float *quats, int64_t n_img,
   last.accumulate = (flags & SPFEL_MERGE_ACCUMULATE) != 0;
   last.mirror1 = last.mirror2 = N;
   e = launch_dft(p->to_modes, cplx ? kCC : kRH, {(int64_t)nfi * nfi, 1, nfi, half}, p->acc, p->t1, first, s);
-  p->acc_zero = e == hipSuccess && !recorded;
+  if (e == hipSuccess) p->acc_replays = replays;
+  p->acc_zero = e == hipSuccess && !recorded && !replays;
   if (e == hipSuccess)
     e = launch_dft(p->to_modes, kCC, {(int64_t)nfi * half, half, nfi, N}, p->t1, p->t2, none, s);
   if (e == hipSuccess)

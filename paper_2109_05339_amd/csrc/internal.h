@@ -64,6 +64,7 @@ struct Plan {
   bool model_set = false;
   bool pending = false;  // deferred spreads are waiting in acc
   bool acc_zero = false; // acc holds zeros (the transform that reads it clears it)
+  bool acc_replays = false;   // a recorded merge leaves sums in acc whenever its graph is replayed
   size_t bytes = 0;
   // Events of the two-stream orientation pipeline (spfel_orient): the main
   // stream's start, each slice buffer's fill and release.

@@ -88,3 +88,28 @@ def test_recorded_merges_do_not_count_as_run(domain):
         eager.append(host(plan.merge_adjoint(q, None, v)))
     for got in eager:   # float atomics in any order: a few roundings per cell
         assert rel(got, ref) <= 1e-5
+
+
+@pytest.mark.parametrize("domain", [spfel.REAL, spfel.COMPLEX])
+def test_replays_of_a_recorded_deferred_merge_stay_out_of_later_merges(domain):
+    """A deferred merge that is recorded leaves its sums in the accumulator on
+    each replay.  After an eager merge has finished it, a replay that nothing
+    finishes is not part of the next complete merge."""
+    det = synth.detector_q(24).astype(np.float32)
+    q = gpu(synth.quaternions(synth.config(4), "image_quats", 9))
+    dtype = torch.float32 if domain == spfel.REAL else torch.complex64
+    v = gpu(np.random.default_rng(3).standard_normal((9, len(det))), dtype)
+    plan = spfel.Plan(25, domain=domain, device=DEV)
+    plan.set_detector(gpu(det))
+    ref = host(plan.merge_adjoint(q, None, v))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.merge_adjoint(q, None, v, flags=spfel.MERGE_DEFER)
+    graph.replay()
+    assert rel(host(plan.merge_adjoint(q, None, v)), 2 * ref) <= 1e-5   # finishes the deferred one
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        for _ in range(2):
+            assert rel(host(plan.merge_adjoint(q, None, v)), ref) <= 1e-5
