@@ -681,7 +681,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_normal_kernel(Geo f, Geo b
 // real density and, with it, of F[-k] = conj f.  The next density is the real
 // part of the inverse transform, that is the inverse transform of the
 // Hermitian part (G[k] + conj G[-k]) / 2 of the projected spectrum: with
-// G[+-k] = amp[+-k] f / |f| where measured (amp where f = 0) and f elsewhere.
+// G[+-k] = amp[+-k] f / |f| where measured (amp where |f| is 0 or no number)
+// and f elsewhere; an f that neither side keeps is replaced, whatever it is.
 // k2_self: the mirror image lies in the half spectrum itself and counts its
 // own error.
 struct Amps {
@@ -708,7 +709,8 @@ __device__ inline float2 project(float2 f, const Amps &m, bool k2_self, float &e
     w += m.am;
     keep -= 1.f;
   }
-  return make_float2(0.5f * fmaf(w, u.x, keep * f.x), 0.5f * fmaf(w, u.y, keep * f.y));
+  const float2 kept = keep > 0.f ? make_float2(keep * f.x, keep * f.y) : make_float2(0.f, 0.f);
+  return make_float2(0.5f * fmaf(w, u.x, kept.x), 0.5f * fmaf(w, u.y, kept.y));
 }
 
 // The amplitudes at (k0, k1, k2) and at its mirror image, axes of n.
