@@ -59,6 +59,7 @@ struct DftLines {
 struct DftEpilogue {
   bool accumulate = false;
   bool clear_in = false;   // zeros the lines once read (kToModes on contiguous lines)
+  int64_t even_lines = 0;  // kToGrid, kRH: transforms the even part of 3D arrays of this many lines each
   int mirror1 = 0, mirror2 = 0;
   const void *lam_v = nullptr;
   const float *lambda = nullptr;   // host values, one per system
@@ -82,8 +83,8 @@ bool dft_phase_fits(const DftTable &tab);
 
 // Axis-0 pass of the normal equations in place on X (n systems of [N][cols]
 // complex columns): to the grid, times That ([L][cols]), back to the modes.
-// cplx = false: the grid values' imaginary parts are dropped before the
-// product (the transform of the even part of a real vector).
+// cplx = false: the columns come from an even real vector, whose grid values
+// are real; what rounding leaves in their imaginary parts is dropped.
 hipError_t launch_dft_normal(const DftTable &to_grid, const DftTable &to_modes, bool cplx,
                              float2 *X, const float2 *That, int n, int64_t cols, hipStream_t s);
 

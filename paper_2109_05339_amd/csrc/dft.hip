@@ -162,6 +162,21 @@ __device__ inline Raw<KIND> load_slot(const Geo &g, const void *in, uint32_t bas
   return r;
 }
 
+// The same slot of the even part of a real 3D array (kToGrid, axis 2): `mirror`
+// is where the line of the opposite modes of the other axes starts.  Halved
+// sums of opposite elements, formed before anything is rounded: an odd array
+// gives zeros.
+__device__ inline Raw<kToGrid> load_even_slot(const Geo &g, const void *in, uint32_t base, uint32_t mirror,
+                                              int slot, bool ok) {
+  const Raw<kToGrid> a = load_slot<kToGrid, kRH>(g, in, base, 1, slot, ok);
+  const Raw<kToGrid> b = load_slot<kToGrid, kRH>(g, in, mirror, 1, slot, ok);
+  const bool zero = slot == 0;   // mode 0 is its own opposite: b.x[1] is not loaded
+  Raw<kToGrid> r;
+  r.x[0] = make_float2(0.5f * (a.x[0].x + (zero ? b.x[0].x : b.x[1].x)), 0.f);
+  r.x[1] = make_float2(zero ? 0.f : 0.5f * (a.x[1].x + b.x[0].x), 0.f);
+  return r;
+}
+
 // Folds a loaded slot into its vector(s) of V.
 template <int KIND, int IO>
 __device__ inline void fold_slot(const Geo &g, const Raw<KIND> &r, int slot, int col,
@@ -376,6 +391,7 @@ __device__ inline void zero_row(const Geo &g, const typename Vec<CPLX>::T *V, F 
 constexpr int kMaxLambdas = 16;
 struct Tail {
   bool accumulate, clear_in;
+  uint32_t even_lines;
   int mirror1, mirror2, half;
   const void *lam_v;
   float lambda[kMaxLambdas];
@@ -443,7 +459,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
         for (int u = 0; u < 4; ++u) {
           const int col = col0 + u * nw;
           const bool ok = col < kCol && c0 + col < cols;
-          raw[u] = load_slot<KIND, IO>(g, in, ok ? (c0 + col) * (uint32_t)len_in : 0, 1, sl, ok);
+          const uint32_t base = ok ? (c0 + col) * (uint32_t)len_in : 0;
+          if constexpr (KIND == kToGrid && IO == kRH) {
+            if (tail.even_lines) {   // lines per array, in the order of the other axes' modes
+              const uint32_t c = ok ? c0 + col : 0, r = c % tail.even_lines;
+              raw[u] = load_even_slot(g, in, base, (c - r + tail.even_lines - 1 - r) * (uint32_t)len_in, sl, ok);
+              continue;
+            }
+          }
+          raw[u] = load_slot<KIND, IO>(g, in, base, 1, sl, ok);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -563,9 +587,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_kernel(Geo g, const void *
 // ------------------------------------------------- fused middle passes ----
 // Normal equations, axis 0: the columns of X are taken to the grid, the grid
 // values multiplied by the kernel's transform, and taken back, all within
-// the block.  CPLX = false drops the grid values' imaginary parts first
-// (the transform of the even part of a real vector), so the forward sums are
-// the real form's.  The block walks over the n systems of its column tile,
+// the block.  CPLX = false: the grid values are those of an even real vector,
+// hence real; what rounding leaves in their imaginary parts is dropped, so the
+// forward sums are the real form's.  The block walks over the n systems of its column tile,
 // the kernel's transform at its cells in registers (PRE: one row tile per
 // wavefront) and the next system's inputs on their way.
 template <bool CPLX, bool PRE>
@@ -946,6 +970,7 @@ hipError_t launch_dft(const DftTable &tab, int io, const DftLines &ln, const voi
   Tail t{};
   t.accumulate = ep.accumulate;
   t.clear_in = ep.clear_in;
+  t.even_lines = (uint32_t)ep.even_lines;
   t.mirror1 = ep.mirror1;
   t.mirror2 = ep.mirror2;
   t.half = ep.mirror1 > 0 ? (int)(ln.cols / ep.mirror1) : 1;

@@ -7,9 +7,10 @@
 // convolution equals the linear one for |k - k'| <= N - 1 < L / 2, so one
 // application is three separable line transforms N -> L, a pointwise
 // product with the transformed kernel, and three line transforms L -> N.
-// REAL domain: the transform of a real vector is Hermitian, so axis 2 keeps
-// its nonnegative half, and the even part of the vector is the real part of
-// its transform, taken before the product.
+// REAL domain: the first line transform reads the even part of the vector (a
+// line and the line of the opposite modes); its transform is real and
+// Hermitian, so axis 2 keeps its nonnegative half, and what rounding leaves in
+// the imaginary parts is dropped before the product.
 // Conjugate gradients solve up to kMaxSystems systems (one per lambda) at
 // once, sharing every transform launch; the step sizes stay on the device.
 #include <cmath>
@@ -296,8 +297,9 @@ static hipError_t normal_apply(const Normal &nm, const void *v, int n, const Lam
   const int64_t N = nm.N, L = nm.L, Lh = nm.Lh;
   const bool cplx = nm.domain == SPFEL_COMPLEX;
   const int64_t cols = L * Lh;
-  DftEpilogue none, last;
-  hipError_t e = launch_dft(nm.F, cplx ? kCC : kRH, {n * N * N, 1, (int)N, (int)Lh}, v, nm.X1, none, st);
+  DftEpilogue first, none, last;
+  first.even_lines = cplx ? 0 : N * N;
+  hipError_t e = launch_dft(nm.F, cplx ? kCC : kRH, {n * N * N, 1, (int)N, (int)Lh}, v, nm.X1, first, st);
   if (e == hipSuccess)
     e = launch_dft(nm.F, kCC, {n * N * Lh, (int)Lh, (int)N, (int)L}, nm.X1, nm.X2, none, st);
   if (e != hipSuccess) return e;

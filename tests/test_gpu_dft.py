@@ -130,3 +130,28 @@ def test_grid_transforms_against_oracle(real, N):
     assert rel_np(host(out), want) <= 1e-5
     plan.merge_adjoint(gpu(q), gpu(det), gpu(y, dt), out=out, flags=spfel.MERGE_ACCUMULATE)
     assert rel_np(host(out), 2 * want) <= 1e-5
+
+
+@pytest.mark.parametrize("N", [3, 7, 33, 65, 131])
+def test_normal_operator_takes_the_even_part_before_it_rounds(N):
+    """REAL: A^T D A acts on the even part of a vector, so an odd one leaves
+    lambda v alone, exactly; and a vector whose odd part is 1e4 times its even
+    part is as accurate as any other (halved sums of opposite elements carry one
+    rounding; the bar of the operator's test above)."""
+    L, M = 2 * N, 2 * N - 1
+    psf = randn(N, (M, M, M), True)
+    w = randn(N + 1, (N, N, N), True)
+    odd = w - w.flip(0, 1, 2)
+    mixed = w + 1e4 * odd
+    lam = 0.25 * M ** 1.5
+    nm = spfel.Normal(N, max_systems=2, device=DEV)
+    nm.set_psf(psf)
+    y = nm.apply(torch.stack([odd, mixed]), [lam, 0.0])
+    assert torch.equal(y[0], np.float32(lam) * odd)
+    m = (torch.arange(M, device=DEV) - (N - 1)) % L
+    big = torch.zeros((L, L, L), dtype=torch.complex128, device=DEV)
+    big[m[:, None, None], m[None, :, None], m[None, None, :]] = psf.to(torch.complex128)
+    x = mixed.double()
+    e = 0.5 * (x + x.flip(0, 1, 2))
+    want = torch.fft.ifftn(torch.fft.fftn(e, s=(L, L, L)) * torch.fft.fftn(big))[:N, :N, :N].real
+    assert rel(y[1], want) <= 2e-5, rel(y[1], want)
