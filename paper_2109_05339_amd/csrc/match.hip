@@ -462,7 +462,7 @@ __device__ inline void insert8(unsigned long long (&top)[8], unsigned long long 
 // 216 us (4,096); at P = 16,384 288 tiles 1,006 / 928 us, 320 tiles 1,010 / 957
 // us, 512 tiles 1,149 / 1,488 us.
 int match_bf16_tile_rows(int64_t M, int64_t N, int64_t P, const void *S, const void *D) {
-  if (P % 64 != 0 || !al16(S) || !al16(D)) return 128;
+  if (P <= 0 || P % 64 != 0 || !al16(S) || !al16(D)) return 128;   // (their first K step is loaded unasked)
   const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
   return big > 136 && (big <= 256 || big > 336) ? 256 : 128;
 }

@@ -72,3 +72,21 @@ def test_fp32_distances_do_not_depend_on_the_tile_size(P):
     same = got[0][0][:50] == got[1][0]   # a row past the first 100 may be nearer at short P
     assert same.mean() >= (0.9 if P >= 96 else 0.1)
     np.testing.assert_array_equal(got[0][1][:50][same], got[1][1][same])
+
+
+@pytest.mark.parametrize("mode", [spfel.MATCH_FP32, spfel.MATCH_BF16_RESCORE8])
+@pytest.mark.parametrize("M,N", [(3, 5), (300, 200), (1500, 1500), (3400, 3400)])
+def test_rows_of_no_pixels(mode, M, N):
+    """P = 0 through the C ABI (a tensor of no columns has no address): every
+    distance is 0 and model image 0 the nearest, and no row is read, also where
+    rows of whole K steps would go to the large tiles (3,400 x 3,400)."""
+    none = torch.zeros(64, device=DEV)
+    zm, zn = torch.zeros(M, device=DEV), torch.zeros(N, device=DEV)
+    bi, bd = spfel.new_best(N, DEV)
+    ws = torch.empty(spfel.match_workspace_bytes(M, N, 0, mode), dtype=torch.uint8, device=DEV)
+    p = none.data_ptr()
+    code = spfel.lib().spfel_match(p, zm.data_ptr(), p, zn.data_ptr(), M, N, 0, 0, mode, p, p, zm.data_ptr(),
+                                   zn.data_ptr(), bi.data_ptr(), bd.data_ptr(), None, ws.data_ptr(), ws.numel(),
+                                   torch.cuda.current_stream().cuda_stream)
+    assert code == 0
+    assert np.all(host(bi) == 0) and np.all(host(bd) == 0.0)
