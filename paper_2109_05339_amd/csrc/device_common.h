@@ -54,15 +54,17 @@ __device__ inline bool support_split(double t, int nf, int &base, float &frac) {
 // and psi >= 2^-c > 2^-126 stays a normal number, so no denormal handling
 // is needed.
 template <int W>
-__device__ inline void es_weights(float frac, float beta, float (&wt)[W]) {
+__device__ inline float es_weight(float frac, float beta, int a) {
   const float c = beta * 1.44269504088896341f;
   const float k = 2.0f / (float)W;
+  const float z = fmaf(frac, k, -(float)a * k);
+  const float r = fmaxf(fmaf(-z, z, 1.0f), 0.0f);
+  return __builtin_amdgcn_exp2f(fmaf(c, __builtin_amdgcn_sqrtf(r), -c));
+}
+template <int W>
+__device__ inline void es_weights(float frac, float beta, float (&wt)[W]) {
 #pragma unroll
-  for (int a = 0; a < W; ++a) {
-    const float z = fmaf(frac, k, -(float)a * k);
-    const float r = fmaxf(fmaf(-z, z, 1.0f), 0.0f);
-    wt[a] = __builtin_amdgcn_exp2f(fmaf(c, __builtin_amdgcn_sqrtf(r), -c));
-  }
+  for (int a = 0; a < W; ++a) wt[a] = es_weight<W>(frac, beta, a);
 }
 
 // float -> bfloat16 bits, round to nearest, ties to even (NaN stays NaN).

@@ -53,11 +53,17 @@ __device__ inline void load_cells(const T *__restrict__ u, uint32_t o, T (&v)[W]
 // The support of one point, read from the grid: base is the first cell (in
 // [0, n_f), storage order) along each axis.  A row of the support is W
 // consecutive cells; one that crosses the grid's end is read cell by cell.
-// The planes are not unrolled: with everything unrolled the complex form held
-// 451 registers, one wavefront per SIMD.
-template <int W, bool CPLX, class T>
+// As many planes go together as measured best without slowing any form: their
+// order and number decide what the L1 still holds (200 x 10,089 points of a
+// 130^3 grid, 50 x 40,000 of 258^3: w = 6 COMPLEX one 397 and 670 us, three 318
+// and 596, all 437 and 729; w = 6 REAL one 184 and 390, three 226 and 524; w = 7
+// REAL one 479 and 885, three 461 and 689; w = 7 COMPLEX one 686 and 1,122, all
+// 574 and 928).  psi0 of a plane is computed as the plane is reached: picked from
+// an array by the plane's number it lay in scratch or in LDS (4,096 complex points
+// of a 66^3 grid 20 us instead of 16.6, 16,384 28 us instead of 16.3).
+template <int W, bool CPLX, int kPlanes, class T>
 __device__ inline void gather_support(const T *__restrict__ u, int nf, const int (&base)[3],
-                                      const float (&w0)[W], const float (&w1)[W],
+                                      float frac0, float beta, const float (&w1)[W],
                                       const float (&w2)[W], float &sr, float &si) {
   uint32_t o1[W];   // row offsets of axis 1 (n_f <= 1022: cells index in 32 bits)
 #pragma unroll
@@ -69,7 +75,7 @@ __device__ inline void gather_support(const T *__restrict__ u, int nf, const int
   const uint32_t nf2 = (uint32_t)nf * nf;
   sr = si = 0.f;
   auto planes = [&](auto contiguous) {
-#pragma unroll 1
+#pragma unroll kPlanes
     for (int a = 0; a < W; ++a) {
       int i0 = base[0] + a;
       i0 -= i0 >= nf ? nf : 0;
@@ -101,10 +107,7 @@ __device__ inline void gather_support(const T *__restrict__ u, int nf, const int
         pr = fmaf(w1[b], rr, pr);
         if (CPLX) pi = fmaf(w1[b], ri, pi);
       }
-      // psi0 of plane a (the planes are not unrolled)
-      float wa = w0[0];
-#pragma unroll
-      for (int e = 1; e < W; ++e) wa = a == e ? w0[e] : wa;
+      const float wa = es_weight<W>(frac0, beta, a);
       sr = fmaf(wa, pr, sr);
       if (CPLX) si = fmaf(wa, pi, si);
     }
@@ -115,11 +118,17 @@ __device__ inline void gather_support(const T *__restrict__ u, int nf, const int
     planes(std::false_type{});
 }
 
+template <int W, bool CPLX>
+constexpr int point_planes() { return W == 7 ? (CPLX ? 7 : 3) : W == 6 && CPLX ? 3 : 1; }
+// ... beside the staging, where more of them do not fit the registers at w = 7
+template <int W, bool CPLX>
+constexpr int tile_planes() { return W == 6 && CPLX ? 3 : 1; }
+
 // Per-point gather for points given with the call.  What bounds it is the
 // traffic of the reads from L2 (the points of the wavefronts on a CU reach far
 // more cells than the L1 holds), so they are as wide as they can be: 200 x
-// 10,089 complex points of a 130^3 grid took 547 us with 8-byte loads and
-// unrolled planes, 385 us here (603 us with 8-byte loads).
+// 10,089 complex points of a 130^3 grid took 557 us with 8-byte loads and
+// everything unrolled, 318 us here.
 template <int W, bool CPLX>
 __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
     const void *__restrict__ u_, int nf, float beta, const double *__restrict__ rot, int64_t M,
@@ -143,11 +152,10 @@ __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
   }
   float sr = __uint_as_float(0x7fc00000u), si = sr;
   if (ok) {
-    float w0[W], w1[W], w2[W];
-    es_weights<W>(frac[0], beta, w0);
+    float w1[W], w2[W];
     es_weights<W>(frac[1], beta, w1);
     es_weights<W>(frac[2], beta, w2);
-    gather_support<W, CPLX>(static_cast<const T *>(u_), nf, base, w0, w1, w2, sr, si);
+    gather_support<W, CPLX, point_planes<W, CPLX>()>(static_cast<const T *>(u_), nf, base, frac[0], beta, w1, w2, sr, si);
   }
   if (!out_) return;
   if constexpr (CPLX)
@@ -168,8 +176,8 @@ __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
 // What bounds it (REAL, w = 6, 65^3 model, 2,048 images of 128^2 pixels,
 // 0.92 ms): the LDS is busy 93% of the time, 43% of that with bank conflicts of
 // the gather, and the vector units three quarters of it.
-// LDS budget of a brick: 29 KB of float (5 blocks per CU, the kernel then
-// fits in 81 registers) or 64 KB of float2 cells.
+// LDS budget of a brick: 29 KB of float (5 blocks per CU, which leaves a
+// wavefront 96 registers; w = 6 takes 90) or 64 KB of float2 cells.
 template <bool CPLX>
 constexpr int brick_bytes() { return CPLX ? 65536 : 29696; }
 
@@ -456,7 +464,7 @@ __global__ __launch_bounds__(kTile, CPLX ? 4 : 5) void interp_tiled_kernel(
       int base[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) base[d] = wrap_mod(l0[d] + (nf >> 1), nf);
-      gather_support<W, CPLX>(u, nf, base, w0, w1, w2, sr, si);
+      gather_support<W, CPLX, tile_planes<W, CPLX>()>(u, nf, base, frac[0], beta, w1, w2, sr, si);
     }
   };
   // The whole tile shares a brick where that fits (16 x 16 points up to about
@@ -496,14 +504,15 @@ static hipError_t interp_w(const Plan &pl, const double *rot, int64_t M, const f
     const int tiles = (int)((P + kTile - 1) / kTile);
     const int64_t blocks = M * tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(kTile);
+#define SPFEL_TILED(C)                                                                             \
+  hipLaunchKernelGGL((interp_tiled_kernel<W, C>), grid, block, 0, s, pl.u, pl.nf, (float)pl.beta,  \
+                     rot, M, pl.det_sorted, pl.det_perm, P, tiles, out)
     if (cplx)
-      hipLaunchKernelGGL((interp_tiled_kernel<W, true>), dim3((unsigned)blocks), dim3(kTile), 0, s,
-                         pl.u, pl.nf, (float)pl.beta, rot, M, pl.det_sorted, pl.det_perm, P,
-                         tiles, out);
+      SPFEL_TILED(true);
     else
-      hipLaunchKernelGGL((interp_tiled_kernel<W, false>), dim3((unsigned)blocks), dim3(kTile), 0,
-                         s, pl.u, pl.nf, (float)pl.beta, rot, M, pl.det_sorted, pl.det_perm, P,
-                         tiles, out);
+      SPFEL_TILED(false);
+#undef SPFEL_TILED
     return hipGetLastError();
   }
   const int64_t total = M * P;
