@@ -171,7 +171,8 @@ __global__ __launch_bounds__(256, 4) void interp_gather_kernel(
 // points' support cells span a small axis-aligned brick of the fine grid,
 // which the block stages in LDS with coalesced row reads; the w^3 gather then
 // reads LDS instead of L1/L2.  A tile whose brick exceeds the LDS budget (a
-// detector that is coarse against the grid) is staged in parts.
+// detector that is coarse against the grid) is staged in parts, or reads the
+// grid (PARTS = false).
 //
 // What bounds it (REAL, w = 6, 65^3 model, 2,048 images of 128^2 pixels,
 // 0.92 ms): the LDS is busy 93% of the time, 43% of that with bank conflicts of
@@ -231,7 +232,7 @@ __device__ inline BrickBox<W, VEC> brick_of(const int (*red)[6], int first, int 
   return b;
 }
 
-template <int W, bool CPLX>
+template <int W, bool CPLX, bool PARTS>
 __global__ __launch_bounds__(kTile, CPLX ? 4 : 5) void interp_tiled_kernel(
     const void *__restrict__ u_, int nf, float beta, const double *__restrict__ rot, int64_t M,
     const float *__restrict__ dets, const int32_t *__restrict__ perm, int64_t P, int tiles,
@@ -477,6 +478,16 @@ __global__ __launch_bounds__(kTile, CPLX ? 4 : 5) void interp_tiled_kernel(
   const BrickBox<W, kVec> all = brick_of<W, kVec>(red, 0, 4);
   if (all.fits(kCap)) {
     pass(std::true_type{}, all, 0, 4);
+  } else if constexpr (!PARTS) {
+    if (valid) {
+      int base[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) base[d] = wrap_mod(l0[d] + (nf >> 1), nf);
+      float w1[W], w2[W];
+      es_weights<W>(frac[1], beta, w1);
+      es_weights<W>(frac[2], beta, w2);
+      gather_support<W, CPLX, tile_planes<W, CPLX>()>(u, nf, base, frac[0], beta, w1, w2, sr, si);
+    }
   } else {
     const int gw = brick_of<W, kVec>(red, 0, 2).fits(kCap) && brick_of<W, kVec>(red, 2, 2).fits(kCap) ? 2 : 1;
 #pragma unroll 1
@@ -496,6 +507,17 @@ __global__ __launch_bounds__(kTile, CPLX ? 4 : 5) void interp_tiled_kernel(
     static_cast<float *>(out_)[o] = sr;
 }
 
+// Launches of few blocks leave CUs idle, and a block that stages its tile in
+// parts does so four times in turn: up to this many blocks a tile whose brick
+// does not fit reads the grid instead (what four parts cost a block stays, what
+// reading the grid costs the memory grows with the blocks).  Whole calls, w = 6,
+// grid reads and parts: REAL 256 blocks 14.0 and 22.2 us (65^3, 64^2 pixels) and
+// 19.6 and 27.6 (129^3, 128^2), 384 blocks 36.2 and 31.0, 512 blocks 25.7 and
+// 24.0 and 43.0 and 34.1; COMPLEX 256 blocks 19.5 and 28.8, 512 blocks 31.6 and
+// 33.3, 1,024 blocks 53.8 and 56.7 and 71.9 and 73.2, 1,536 blocks 98.5 and 97.6.
+template <bool CPLX>
+constexpr int64_t few_blocks() { return CPLX ? 1024 : 256; }
+
 template <int W>
 static hipError_t interp_w(const Plan &pl, const double *rot, int64_t M, const float *detq,
                            int64_t P, void *out, hipStream_t s) {
@@ -505,13 +527,18 @@ static hipError_t interp_w(const Plan &pl, const double *rot, int64_t M, const f
     const int64_t blocks = M * tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(kTile);
-#define SPFEL_TILED(C)                                                                             \
-  hipLaunchKernelGGL((interp_tiled_kernel<W, C>), grid, block, 0, s, pl.u, pl.nf, (float)pl.beta,  \
-                     rot, M, pl.det_sorted, pl.det_perm, P, tiles, out)
-    if (cplx)
-      SPFEL_TILED(true);
+#define SPFEL_TILED(C, PARTS)                                                                      \
+  hipLaunchKernelGGL((interp_tiled_kernel<W, C, PARTS>), grid, block, 0, s, pl.u, pl.nf,           \
+                     (float)pl.beta, rot, M, pl.det_sorted, pl.det_perm, P, tiles, out)
+    const bool parts = blocks > (cplx ? few_blocks<true>() : few_blocks<false>());
+    if (cplx && parts)
+      SPFEL_TILED(true, true);
+    else if (cplx)
+      SPFEL_TILED(true, false);
+    else if (parts)
+      SPFEL_TILED(false, true);
     else
-      SPFEL_TILED(false);
+      SPFEL_TILED(false, false);
 #undef SPFEL_TILED
     return hipGetLastError();
   }

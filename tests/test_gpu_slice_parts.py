@@ -37,3 +37,26 @@ def test_parts_of_a_tile_equal_the_per_point_path(w, domain, scale):
     b = host(plan.slice(gpu(q), gpu(det))[0])
     np.testing.assert_array_equal(a, b)
     assert np.all(np.isnan(a[3])) and np.all(np.isfinite(a[[0, 1, 2, 4]]))
+
+
+# (blocks = 10 tiles per row) on both sides of the launches that read the grid
+# instead of staging parts: REAL 250 and 260 blocks, COMPLEX 1,020 and 1,030
+@pytest.mark.parametrize("w,domain,rows", [(6, spfel.REAL, 25), (6, spfel.REAL, 26), (6, spfel.COMPLEX, 102),
+                                           (6, spfel.COMPLEX, 103), (4, spfel.REAL, 30), (8, spfel.COMPLEX, 104),
+                                           (7, spfel.REAL, 26)])
+@pytest.mark.parametrize("scale", [0.5, 1.0, 1.6, 3.0])
+def test_many_and_few_blocks_equal_the_per_point_path(w, domain, rows, scale):
+    det = detector(50) * scale
+    q = synth.quaternions(synth.config(1), "ref_quats", rows)
+    q[3] = 0.0
+    plan = spfel.Plan(33, kernel_width=w, domain=domain, device=DEV)
+    m = model(1)
+    if domain == spfel.REAL:
+        plan.set_model(gpu(m))
+    else:
+        plan.set_model(gpu(synth.complex_perturbation(synth.config(4), m), torch.complex64))
+    plan.set_detector(gpu(det))
+    a = host(plan.slice(gpu(q))[0])
+    b = host(plan.slice(gpu(q), gpu(det))[0])
+    np.testing.assert_array_equal(a, b)
+    assert np.all(np.isnan(a[3])) and np.all(np.isfinite(np.delete(a, 3, axis=0)))
