@@ -453,18 +453,28 @@ __device__ inline void insert8(unsigned long long (&top)[8], unsigned long long 
   }
 }
 
-// The large-tile kernel is used when its 256 x 256 tiles occupy more than
-// half of the chip's 256 resident blocks, and where a second round of them is
-// at least a third full, P is a whole number of its 64-wide K steps and both
-// operands are 16-byte aligned; otherwise 128 x 128 tiles.  Measured (whole
-// calls), large tiles against 128 x 128: 132 tiles 176 / 175 us (P = 4,096);
-// 144 tiles 173 / 172 us (P = 4,096) and 541 / 566 us (16,384); 256 tiles 182 /
-// 216 us (4,096); at P = 16,384 288 tiles 1,006 / 928 us, 320 tiles 1,010 / 957
-// us, 512 tiles 1,149 / 1,488 us.
+// The large-tile kernel needs rows of whole 64-wide K steps and 16-byte aligned
+// operands; otherwise 128 x 128 tiles.  Its blocks run in rounds of 256 of equal
+// length, of which a last one that is hardly filled is lost, and what its long
+// prologue and epilogue cost weighs more the shorter the rows are.  Measured
+// (whole calls, large tiles : 128 x 128):
+//   several rounds, by the share of their blocks that is used:
+//     P =    256  0.98  140 : 133 us (756 tiles)
+//     P =  1,024  0.88  245 : 239 (900)    0.98  198 : 203 (756)
+//     P =  1,600  0.78  239 : 226 (600)    0.85  241 : 242 (650)  0.95  244 : 259 (729)
+//     P =  2,304  0.75  292 : 267 (576)    0.82  380 : 377 (840)  0.85  297 : 309 (650)
+//     P =  4,096  0.75  438 : 416 (576)    0.78  441 : 449 (600)  0.85  444 : 485 (650)
+//     P =  6,400  0.74  435 : 436 (380)    0.75  634 : 618 (576)  0.78  638 : 666 (600)
+//     P = 16,384  0.60  1,018 : 987 (306)  0.67  1,040 : 1,082 (342)  0.69  1,557 : 1,615 (528)
+//   one round:
+//     144 tiles   P = 256 77 : 72   1,600 104 : 99   3,136 142 : 141   6,400 225 : 230
+//     196 tiles   P = 256 78 : 81   1,600 104 : 117
 int match_bf16_tile_rows(int64_t M, int64_t N, int64_t P, const void *S, const void *D) {
   if (P <= 0 || P % 64 != 0 || !al16(S) || !al16(D)) return 128;   // (their first K step is loaded unasked)
-  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-  return big > 136 && (big <= 256 || big > 336) ? 256 : 128;
+  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256), rounds = (big + 255) / 256;
+  if (rounds == 1) return big > (P >= 3072 ? 136 : 191) ? 256 : 128;
+  const double used = (double)big / (256.0 * (double)rounds);
+  return used >= (P >= 8192 ? 2.0 / 3.0 : 0.72 + 230.0 / (double)P) ? 256 : 128;
 }
 
 // Candidate buffer for the 128-row tiling, the larger of the two.

@@ -90,3 +90,12 @@ def test_rows_of_no_pixels(mode, M, N):
                                    torch.cuda.current_stream().cuda_stream)
     assert code == 0
     assert np.all(host(bi) == 0) and np.all(host(bd) == 0.0)
+
+
+# BF16 launches on both sides of the rule for the 256-row tiles: one round of
+# them (182 and 196 of short rows, 132 and 144 of long ones) and two rounds of
+# which 0.87 and 0.95 are used, at a row length that needs 0.93
+@pytest.mark.parametrize("M,N,P", [(3500, 3300, 64), (3500, 3500, 64), (3000, 2800, 3072), (3000, 3000, 3072),
+                                   (5500, 5300, 1088), (5500, 5600, 1088)])
+def test_sizes_of_the_large_tiles(M, N, P):
+    test_split_and_ragged_launches(spfel.MATCH_BF16_RESCORE8, M, N, P)
