@@ -357,7 +357,7 @@ int spfel_plan_create(spfel_plan *out, int n_model, int kernel_width,
     }
   }
   e = hipMemcpy(p->wpos, wp.data(), tab_grid, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = dft_table_fill(p->to_modes, -1, false, deconvolve);
+  if (e == hipSuccess) e = dft_table_fill(p->to_modes, -1, deconvolve);
   if (e != hipSuccess) {
     free_plan(p);
     delete p;

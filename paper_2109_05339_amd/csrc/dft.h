@@ -36,12 +36,13 @@ struct DftTable {
   float2 *t = nullptr;
 };
 
-// Host part of a table: sizes and values.  weight(k) multiplies mode (or
-// output frequency) k; sign is that of the exponent; centred: grid index i
-// holds cell i - H.  Returns the device bytes of the table.
+// Host part of a table: its sizes (returns its bytes, a multiple of 16), its
+// values (t: that many bytes of host memory), and the values sent to the device.
+// weight(k) multiplies mode (or output frequency) k; sign is that of the exponent.
 size_t dft_table_sizes(DftTable &tab, int kind, int h, int H);
-hipError_t dft_table_fill(DftTable &tab, int sign, bool centred,
-                          const std::function<double(int)> &weight);
+void dft_table_values(const DftTable &tab, int sign, const std::function<double(int)> &weight,
+                      float2 *t);
+hipError_t dft_table_fill(DftTable &tab, int sign, const std::function<double(int)> &weight);
 
 // Lines of one launch: element e of column c = (a, b), b < B, is at
 // (a len + e) B + b on either side, with that side's len.

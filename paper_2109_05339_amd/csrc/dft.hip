@@ -867,6 +867,10 @@ __global__ __launch_bounds__(256) void phase_projection_kernel(float2 *__restric
 // --------------------------------------------------------------- host ----
 static int up(int v, int m) { return (v + m - 1) / m * m; }
 
+static size_t table_bytes(const DftTable &tab) {
+  return (size_t)tab.tiles * (tab.slots / 4) * 64 * sizeof(float2) + tab.slots * sizeof(float);
+}
+
 size_t dft_table_sizes(DftTable &tab, int kind, int h, int H) {
   tab.kind = kind;
   tab.h = h;
@@ -882,16 +886,16 @@ size_t dft_table_sizes(DftTable &tab, int kind, int h, int H) {
     tab.even_tiles = up(h / 2, 16) / 16;
     tab.tiles = tab.even_tiles + up((h + 1) / 2, 16) / 16;
   }
-  return (size_t)tab.tiles * (tab.slots / 4) * 64 * sizeof(float2) + tab.slots * sizeof(float);
+  return table_bytes(tab);
 }
 
-hipError_t dft_table_fill(DftTable &tab, int sign, bool centred,
-                          const std::function<double(int)> &weight) {
+void dft_table_values(const DftTable &tab, int sign, const std::function<double(int)> &weight,
+                      float2 *t) {
   const int steps = tab.slots / 4;
   const long n = tab.kind == kCyclic ? tab.H : 2L * tab.H;
   const size_t tiled = (size_t)tab.tiles * steps * 64;
-  std::vector<float2> t(tiled + (tab.slots + 1) / 2, make_float2(0.f, 0.f));
-  float *row0 = reinterpret_cast<float *>(t.data() + tiled);
+  std::fill(t, t + tiled + tab.slots / 2, make_float2(0.f, 0.f));
+  float *row0 = reinterpret_cast<float *>(t + tiled);
   // phases reduced modulo the length exactly, float64, rounded once
   std::vector<double> co(n), si(n);
   for (long j = 0; j < n; ++j) {
@@ -905,7 +909,7 @@ hipError_t dft_table_fill(DftTable &tab, int sign, bool centred,
   };
   auto put = [&](long cell, long mode, float2 &v) {
     if (2 * cell > tab.H || (tab.kind == kCyclic ? 2 * mode > tab.H : mode > tab.h)) return;
-    const double w = weight((int)mode) * (centred && (mode & 1) ? -1.0 : 1.0);
+    const double w = weight((int)mode);
     const long ph = (cell * mode) % n;
     v = make_float2((float)(co[ph] * w), (float)(si[ph] * w));
   };
@@ -929,7 +933,12 @@ hipError_t dft_table_fill(DftTable &tab, int sign, bool centred,
       put(slot, 0, v);
     row0[slot] = v.x;
   }
-  return hipMemcpy(tab.t, t.data(), tiled * sizeof(float2) + tab.slots * sizeof(float), hipMemcpyHostToDevice);
+}
+
+hipError_t dft_table_fill(DftTable &tab, int sign, const std::function<double(int)> &weight) {
+  std::vector<float2> t(table_bytes(tab) / sizeof(float2));
+  dft_table_values(tab, sign, weight, t.data());
+  return hipMemcpy(tab.t, t.data(), table_bytes(tab), hipMemcpyHostToDevice);
 }
 
 // Wavefronts per block: one per row tile up to eight, rounded to 2, 4 or 8.

@@ -410,9 +410,9 @@ int spfel_normal_create(spfel_normal *out, int n_model, int domain, int max_syst
     p->bytes += r.bytes;
   }
   const double scale = 1.0 / (double)L;
-  e = dft_table_fill(p->F, -1, false, [](int) { return 1.0; });
-  if (e == hipSuccess) e = dft_table_fill(p->G, +1, false, [&](int) { return scale; });
-  if (e == hipSuccess) e = dft_table_fill(p->Hm, -1, false, [](int) { return 1.0; });
+  e = dft_table_fill(p->F, -1, [](int) { return 1.0; });
+  if (e == hipSuccess) e = dft_table_fill(p->G, +1, [&](int) { return scale; });
+  if (e == hipSuccess) e = dft_table_fill(p->Hm, -1, [](int) { return 1.0; });
   if (prev != device) (void)hipSetDevice(prev);
   if (e != hipSuccess) {
     free_normal(p);
