@@ -269,7 +269,7 @@ __device__ inline float split_sum(const float *__restrict__ part, int splits, in
 
 // Epilogue of a split launch: a block takes 32 columns of a tile, a thread 16
 // (tiles of 64: 8) rows of one of them.
-constexpr int kRedCols = 32, kRedRows = kBM / (256 / kRedCols);
+constexpr int kRedCols = 32;
 
 template <int T>
 __global__ __launch_bounds__(256) void reduce_f32_kernel(
@@ -383,8 +383,9 @@ static bool f32_small(int64_t M, int64_t N, int64_t P) {
 }
 
 // Packed keys first.  A launch that splits K has its partial tiles at the
-// offset below: callers size their workspaces by this rule, with a reserved
-// word per 128 x 128 tile between the two (tiles of 64 never need more).
+// offset below.  The word per 128 x 128 tile between the two is not used: it
+// keeps the size that spfel_match_workspace_bytes has always given, which
+// callers may have stored (tiles of 64 never need more).
 static size_t f32_partials_at(int64_t M, int64_t N) {
   const size_t keys = ((size_t)N * sizeof(unsigned long long) + 255) & ~(size_t)255;
   return keys + (((size_t)tiles_of(M, N, kBM) * sizeof(unsigned) + 255) & ~(size_t)255);
