@@ -155,3 +155,67 @@ def test_normal_operator_takes_the_even_part_before_it_rounds(N):
     e = 0.5 * (x + x.flip(0, 1, 2))
     want = torch.fft.ifftn(torch.fft.fftn(e, s=(L, L, L)) * torch.fft.fftn(big))[:N, :N, :N].real
     assert rel(y[1], want) <= 2e-5, rel(y[1], want)
+
+
+def reduction_step(rho, amp, seen, sup):
+    """One error reduction step without positivity in float64, and its error."""
+    v, err = phase_step(rho, amp, seen, torch.ones_like(sup), 0.0)
+    return torch.where(sup.bool(), v, torch.zeros_like(v)), err
+
+
+# Error reduction runs on the line transforms (HIO on full tables): their cyclic
+# form with one to nineteen tiles of 16 rows, more tiles than wavefronts from 258
+# on, and at 602 the axis-0 passes and the projection apart.  Tolerances as above.
+@pytest.mark.parametrize("N", [2, 3, 4, 7, 31, 32, 33, 34, 64, 65, 66, 100, 128, 129, 130, 258, 602])
+def test_error_reduction_step_against_float64_ffts(N):
+    rho = randn(N, (N, N, N), True)
+    amp = randn(N + 1, (N, N, N), True).abs() * N ** 1.5
+    seen = (randn(N + 2, (N, N, N), True) > -0.7).to(torch.uint8)
+    sup = (randn(N + 3, (N, N, N), True) > 0).to(torch.uint8)
+    p = spfel.Phase(N, device=DEV)
+    for mask in (seen, None):   # None: all coefficients measured
+        want, err = reduction_step(rho, amp, torch.ones_like(seen) if mask is None else mask, sup)
+        got = rho.clone()
+        e = p.iterate(got, amp, sup, 1, mode=spfel.PHASE_ER, positivity=False, measured=mask, errors=True)
+        assert float(want.norm()) == 0 or rel(got, want) <= 2e-5, rel(got, want)
+        assert abs(float(e[0]) - float(err)) <= 1e-5 * float(err)
+
+
+@pytest.mark.parametrize("N", [7, 34, 65, 130])
+def test_errors_of_a_burst_of_error_reduction_steps(N):
+    """Each step's error is summed by the launch after its projection.  Error
+    reduction does not amplify: five steps carry at most five times a step's
+    bar, and the error, of order 1 here, twice that."""
+    rho = randn(N, (N, N, N), True)
+    amp = randn(N + 1, (N, N, N), True).abs() * N ** 1.5
+    seen = (randn(N + 2, (N, N, N), True) > -0.7).to(torch.uint8)
+    sup = (randn(N + 3, (N, N, N), True) > 0).to(torch.uint8)
+    got, want, errs = rho.clone(), rho, []
+    e = spfel.Phase(N, device=DEV).iterate(got, amp, sup, 5, mode=spfel.PHASE_ER, positivity=False,
+                                           measured=seen, errors=True)
+    for _ in range(5):
+        want, err = reduction_step(want, amp, seen, sup)
+        errs.append(float(err))
+    assert rel(got, want) <= 1e-4, rel(got, want)
+    assert np.all(np.abs(host(e) - errs) <= 2e-4 * np.array(errs))
+
+
+def test_real_normal_operator_past_the_fused_pass():
+    """REAL, N = 483: the axis-0 pass does not fit the LDS and runs as two line
+    transforms with the product between them.  Sampled outputs against direct
+    sums over the kernel, each with the bar of the sampled test at N = 129 (1e-5
+    of the root of the sums of squares)."""
+    N, M = 483, 965
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    psf = torch.randn((M, M, M), generator=g, device=DEV)
+    v = torch.randn((1, N, N, N), generator=g, device=DEV)
+    nm = spfel.Normal(N, max_systems=1, device=DEV)
+    nm.set_psf(psf)
+    y = nm.apply(v, [0.5])[0]
+    ve = 0.5 * (v[0].double() + v[0].flip(0, 1, 2).double())
+    for k in ((0, 0, 0), (N - 1, 3, 200), (241, 241, 241), (100, N - 1, N - 2), (17, 311, 0)):
+        win = psf[k[0]:k[0] + N, k[1]:k[1] + N, k[2]:k[2] + N].flip(0, 1, 2).double()
+        want = float((win * ve).sum()) + 0.5 * float(v[0][k])
+        scale = float((win.square().sum() * ve.square().sum()).sqrt())
+        assert abs(float(y[k]) - want) <= 1e-5 * scale, k
