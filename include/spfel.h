@@ -317,10 +317,12 @@ int spfel_weighted_residual(spfel_plan plan, const void *slices,
  * stay on the device (no host synchronisation). */
 
 /* n_model odd in 3..511, domain SPFEL_REAL or SPFEL_COMPLEX, max_systems
- * 1..16, on HIP device `device`.  SPFEL_ENOMEM if the buffers
- * (the transformed kernel and an intermediate as large, 4 (2N)^3 bytes each
- * for REAL and twice that for COMPLEX, and four vectors per system) do not
- * fit. */
+ * 1..16, on HIP device `device`.  SPFEL_ENOMEM if the buffers do not fit.
+ * REAL, in bytes: the transformed kernel 32 N^3; two intermediates of the
+ * systems transformed at once (as many as stay within 208 MB, one at least), 16
+ * N^3 and 8 N^3 per system, and no smaller than setting the kernel needs (32
+ * N^3 each); from about N = 481 on a third, 32 N^3; four vectors of 4 N^3 per
+ * system.  COMPLEX: twice that (the third from about N = 401 on). */
 int spfel_normal_create(spfel_normal *out, int n_model, int domain,
                         int max_systems, int device);
 

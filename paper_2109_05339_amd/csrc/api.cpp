@@ -520,8 +520,10 @@ int spfel_set_model(spfel_plan plan, const void *model, void *stream) {
   // u[l] = sum_k m_k exp(+2 pi i k.l / nf) / (psi_hat psi_hat psi_hat), one
   // axis at a time: axis 2 (N^2 lines), axis 1, axis 0.  By full tables: the
   // grid's rounding reaches the distances of orientation matching, differences
-  // of nearly equal sums, some five hundred times larger (line transforms, 0.10
-  // instead of 0.37 ms at N = 129, moved them by 5e-5 of themselves).
+  // of nearly equal sums, some five hundred times larger.  Line transforms (0.10
+  // instead of 0.32 ms at N = 129) moved them by up to 5e-5 of themselves, to
+  // slightly nearer float64 (65^3: 2.2e-5 to 2.6e-5 away instead of 2.7e-5 to
+  // 2.9e-5); the slices lie equally near either way.
   hipError_t e = launch_contract_rows(model, cplx, p->wpos, p->t1, N * N, N, nf, s);
   if (e == hipSuccess) e = launch_contract(p->t1, p->wpos, p->t2, false, N, N, nf, nf, s);
   if (e == hipSuccess) e = launch_contract(p->t2, p->wpos, p->u, !cplx, 1, N, nf, nf * nf, s);

@@ -25,12 +25,13 @@
 //
 // Measured on an application of the normal equations (N = 129, L = 258, 8
 // REAL systems): 7.1 ms by full complex tables (42% of the FP32 matrix rate
-// on eleven times the products), 0.72 ms here: axis-0 pass 312 us, axis 1
-// 128 and 126 us (415 MB each, 3.3 TB/s), axis 2 73 and 98 us.  One error
-// reduction at N = 129: 329 us by full tables and full spectra, 70 us here
-// (axis-0 pass with the projection 26 us, the others 11 to 13 us each, half
-// of it matrix instructions).  The merge's transform at N = 129: 515 us plus a
-// 17 us clear of the accumulator by full tables, 79 us here.
+// on eleven times the products), 0.74 ms here: axis-0 pass 325 us, axis 1
+// 108 and 110 us (415 MB each, 3.8 TB/s), axis 2 92 us (73 before it read the
+// opposite lines too) and 101 us.  One error reduction at N = 129: 329 us by
+// full tables and full spectra, 70 us here (axis-0 pass with the projection 26
+// us, the others 11 to 13 us each, half of it matrix instructions).  The merge's
+// transform at N = 129: 515 us plus a 17 us clear of the accumulator by full
+// tables, 79 us here.
 //
 // Lane layout of the instruction: lane t supplies A[t % 16][t / 16] and
 // B[t / 16][t % 16] and receives D[4 (t / 16) + j][t % 16], j = 0..3.

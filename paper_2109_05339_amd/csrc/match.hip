@@ -349,8 +349,8 @@ static int64_t tiles_of(int64_t M, int64_t N, int T) { return ((M + T - 1) / T) 
 // resident blocks with 128 x 128 tiles, each split at least 1024 values of P
 // long.  Only launches of under half a round of tiles are split: blocks are
 // dispatched dynamically, so a partial last round costs less than the
-// partial tiles' extra traffic (measured on 1,264 tiles of K = 16,384:
-// unsplit 5.8 ms, two splits 6.7 ms).  The distances are differences of
+// partial tiles' extra traffic (1,264 tiles of K = 16,384: unsplit 5.21 ms,
+// two splits 5.23).  The distances are differences of
 // nearly equal sums, so their rounding shows the order of those: more splits,
 // down to 512 values, moved distances of Poisson images by up to 3e-5 of
 // themselves.
@@ -375,9 +375,9 @@ static int f32_splits(int64_t M, int64_t N, int64_t P) {
 // Blocks of 128 x 128 outputs for fewer than three quarters of the CUs: tiles
 // of a quarter, four times as many blocks of half the matrix instructions per
 // K step and wavefront.  Whole calls, 128- and 64-tiles: one block of 128
-// (128 x 64 x 4,096) 278 and 100 us; 64 (1,000 x 256 x 4,096) 91 and 44; 128
-// (1,000 x 512 x 4,096) 92 and 62; 240 (1,920 x 512 x 4,096) 97 and 102; 480
-// (2,560 x 768 x 4,096) 167 and 175.
+// (128 x 64 x 4,096) 279 and 100 us; 64 (1,000 x 256 x 4,096) 89 and 41; 128
+// (1,000 x 512 x 4,096) 89 and 56; 192 (1,500 x 512 x 4,096) 91 and 93; 240
+// (1,920 x 512 x 4,096) 91 and 95; 480 (2,560 x 768 x 4,096) 153 and 173.
 static bool f32_small(int64_t M, int64_t N, int64_t P) {
   return tiles_of(M, N, kBM) * f32_splits(M, N, P) < kSlots * 3 / 8;
 }
