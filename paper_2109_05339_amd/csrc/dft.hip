@@ -706,7 +706,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void dft_normal_kernel(Geo f, Geo b
 // real density and, with it, of F[-k] = conj f.  The next density is the real
 // part of the inverse transform, that is the inverse transform of the
 // Hermitian part (G[k] + conj G[-k]) / 2 of the projected spectrum: with
-// G[+-k] = amp[+-k] f / |f| where measured (amp where |f| is 0 or no number)
+// G[+-k] = amp[+-k] f / |f| where measured (amp where f is 0 or not finite)
 // and f elsewhere; an f that neither side keeps is replaced, whatever it is.
 // k2_self: the mirror image lies in the half spectrum itself and counts its
 // own error.
@@ -716,7 +716,8 @@ struct Amps {
 };
 __device__ inline float2 project(float2 f, const Amps &m, bool k2_self, float &e, float &a2) {
   const float mag = sqrtf(fmaf(f.x, f.x, f.y * f.y));
-  const float2 u = mag > 0.f ? make_float2(f.x / mag, f.y / mag) : make_float2(1.f, 0.f);
+  float2 u = mag > 0.f ? make_float2(f.x / mag, f.y / mag) : make_float2(1.f, 0.f);
+  if (u.x != u.x || u.y != u.y) u = make_float2(1.f, 0.f);   // infinite f
   float w = 0.f, keep = 2.f;
   if (m.seen) {
     const float d = mag - m.a;

@@ -200,16 +200,17 @@ def test_zero_iterations_change_nothing():
 
 
 @pytest.mark.parametrize("mode", [spfel.PHASE_ER, spfel.PHASE_HIO])
-@pytest.mark.parametrize("N", [8, 33])
-def test_a_measured_coefficient_is_replaced_even_if_it_is_no_number(N, mode):
-    """One NaN in the density makes every coefficient NaN.  Where all of them
-    are measured, each is replaced by its amplitude (the rule for a coefficient
-    without a phase), so the step's density is the inverse transform of the
-    amplitudes within the support."""
+@pytest.mark.parametrize("N", [8, 15, 33])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_a_measured_coefficient_is_replaced_even_if_it_is_not_finite(value, N, mode):
+    """One NaN or infinity in the density makes no coefficient finite.  Where all
+    of them are measured, each is replaced by its amplitude (the rule for a
+    coefficient without a phase), so the step's density is the inverse transform
+    of the amplitudes within the support."""
     _, A, sup = blob_object(1, N)
     sup = np.ones_like(sup)
     x = (np.random.default_rng(2).random((N, N, N))).astype(np.float32)
-    x[1, 2, 3] = np.nan
+    x[1, 2, 3] = value
     A32 = A.astype(np.float32)
     r = gpu(x)
     spfel.Phase(N, device=DEV).iterate(r, gpu(A32), gpu(sup, torch.uint8), 1, mode=mode, positivity=False)
